@@ -172,7 +172,6 @@ __device__ __forceinline__ uint32_t block_add_u32(uint32_t v, uint32_t* red) {
 // crossing at a level, the nearest entry of nonzero mass is taken, so a drawn
 // id always has positive probability.
 constexpr int kSmpThreads = 256;
-constexpr int kSmpWaves = kSmpThreads / 64;
 constexpr int kSmpLoads = 8;                   // loads per lane per step
 constexpr int kSmpStepVecs = 16 * kSmpLoads;   // vectors per DPP-row step (128)
 constexpr int kSmpMaxChunks = 2048;            // records per row
@@ -203,13 +202,14 @@ constexpr double kStepLo = 1.90821492927058770002e-10 / kExpTab;
 constexpr double kQ3 = 0.16666667050025266, kQ2 = 0.50000001916793,
                  kQ1 = 0.9999999999999998, kQ0 = 0.9999999999999989;
 
+template <int T, int MAXC>
 struct SmpLds {
-  double s[kSmpMaxChunks];  // chunk sum at its max; then at the row max
-  float m[kSmpMaxChunks];   // chunk max
-  double p[kSmpThreads];    // inclusive prefix of the runs
-  double tab[kExpTab];      // 2^(j / 512)
-  double wt[kSmpWaves];
-  float red[kSmpWaves];
+  double s[MAXC];       // chunk sum at its max; then at the row max
+  float m[MAXC];        // chunk max
+  double p[T];          // inclusive prefix of the runs
+  double tab[kExpTab];  // 2^(j / 512)
+  double wt[T / 64];
+  float red[T / 64];
 };
 
 // (c2 is kQ2, passed in a vector register: one instruction cannot read two
@@ -282,15 +282,31 @@ __device__ __forceinline__ double row16_sum(double x) {
   x += dpp_move_f64<0x4E>(x);   // quad_perm [2,3,0,1]
   return x;
 }
-// inclusive prefix sum over the 64 lanes of a wavefront, in double
+// inclusive prefix sum over the 64 lanes of a wavefront, in double: row shifts
+// by 1, 2, 4 and 8 within each 16 lanes, then lanes 15 and 31 onto the rows
+// after them (lanes without a source add 0)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_from_f64(double v) {
+  u32x2 h = __builtin_bit_cast(u32x2, v);
+  h[0] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h[0], CTRL, ROWS, 0xF, false);
+  h[1] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h[1], CTRL, ROWS, 0xF, false);
+  return __builtin_bit_cast(double, h);
+}
 __device__ __forceinline__ double wave_incl_scan_f64(double x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double t = __shfl_up(x, o, 64);
-    if (lane >= o) x += t;
-  }
+  x += dpp_from_f64<0x111, 0xF>(x);  // row_shr:1
+  x += dpp_from_f64<0x112, 0xF>(x);  // row_shr:2
+  x += dpp_from_f64<0x114, 0xF>(x);  // row_shr:4
+  x += dpp_from_f64<0x118, 0xF>(x);  // row_shr:8
+  x += dpp_from_f64<0x142, 0xA>(x);  // row_bcast:15 to rows 1 and 3
+  x += dpp_from_f64<0x143, 0xC>(x);  // row_bcast:31 to rows 2 and 3
   return x;
+}
+// a double of one lane, the same in every lane (lane: wave-uniform)
+__device__ __forceinline__ double from_lane(double v, int lane) {
+  u32x2 h = __builtin_bit_cast(u32x2, v);
+  h[0] = (uint32_t)__builtin_amdgcn_readlane((int)h[0], lane);
+  h[1] = (uint32_t)__builtin_amdgcn_readlane((int)h[1], lane);
+  return __builtin_bit_cast(double, h);
 }
 
 __device__ __forceinline__ int first_lane(uint64_t b) { return b ? __ffsll((long long)b) - 1 : -1; }
@@ -299,128 +315,190 @@ __device__ __forceinline__ int last_lane(uint64_t b) { return b ? 63 - __clzll((
 enum Pick : int { kCross = 0, kFirst = 1, kLast = 2 };
 
 // First (or last) chunk in [lo, hi) with positive mass, by wave ballots; -1 if none.
-__device__ __forceinline__ int64_t chunk_positive(const SmpLds& c, int64_t lo, int64_t hi,
+__device__ __forceinline__ int64_t chunk_positive(const double* s, int64_t lo, int64_t hi,
                                                   bool last) {
   const int lane = threadIdx.x & 63;
   if (!last) {
     for (int64_t b = lo; b < hi; b += 64) {
       const int64_t q = b + lane;
-      const int f = first_lane(__ballot(q < hi && c.s[q] > 0.0));
+      const int f = first_lane(__ballot(q < hi && s[q] > 0.0));
       if (f >= 0) return b + f;
     }
   } else {
     for (int64_t b = hi; b > lo; b -= 64) {
       const int64_t q = b - 64 + lane;
-      const int l = last_lane(__ballot(q >= lo && q < b && c.s[q] > 0.0));
+      const int l = last_lane(__ballot(q >= lo && q < b && s[q] > 0.0));
       if (l >= 0) return b - 64 + l;
     }
   }
   return -1;
 }
 
-// The eight terms of this lane's two vectors of the 128-vector step that
-// starts at vector v0 (vectors at or past the chunk end c1 give 0).
+// The terms of a row whose records are kept at their chunk's maximum: exp(z -
+// m_q), to be scaled by f_q = exp(m_q - M).
+struct ExpTerms {
+  const float* m;     // chunk maxima
+  const double* tab;  // 2^(j / 512)
+  double Md;          // row maximum
+  struct Chunk {
+    double md, scale, c2;
+  };
+  __device__ __forceinline__ Chunk chunk(int64_t q) const {
+    const double mq = (double)m[q];
+    return Chunk{mq, exp_neg(mq - Md, tab), c2_reg()};
+  }
+  __device__ __forceinline__ double operator()(float z, const Chunk& k) const {
+    return term(z, k.md, tab, k.c2);
+  }
+  // the record s of chunk q at the row maximum (a NaN record stays NaN: the
+  // row has no distribution)
+  __device__ __forceinline__ double record(int64_t q, double s) const {
+    return m[q] == kNegInf ? 0.0 : s * exp_neg((double)m[q] - Md, tab);
+  }
+};
+
+// This lane's two vectors of the 128-vector step that starts at vector v0, and
+// their eight terms (vectors at or past the chunk end c1 give 0).
 template <class TI>
-__device__ __forceinline__ void step_terms(const void* zrow, uint32_t v0, uint32_t c1,
-                                           uint32_t nvec, int tail, float mq, const double* tab,
-                                           double (&w)[8]) {
-  const double md = (double)mq, c2 = c2_reg();
+__device__ __forceinline__ void step_load(const void* zrow, uint32_t v0, uint32_t c1,
+                                          uint32_t nvec, int tail, typename TI::Vec (&x)[2]) {
   const uint32_t v = v0 + 2u * (uint32_t)(threadIdx.x & 63);
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const bool in = v + h < c1;  // inside the chunk (and so the row)
-    float f[4];
-    unpack<TI>(in ? load_vec<TI>(zrow, v + h, nvec, tail) : neg_inf_vec<TI>(), f);
+    x[h] = neg_inf_vec<TI>();
+    if (v + h < c1) x[h] = load_vec<TI>(zrow, v + h, nvec, tail);
+  }
+}
+template <class TI, class Terms>
+__device__ __forceinline__ void step_terms(const typename TI::Vec (&x)[2], uint32_t v0,
+                                           uint32_t c1, const Terms& terms,
+                                           const typename Terms::Chunk& ck, double (&w)[8]) {
+  const uint32_t v = v0 + 2u * (uint32_t)(threadIdx.x & 63);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) w[4 * h + e] = in ? term(f[e], md, tab, c2) : 0.0;
+  for (int h = 0; h < 2; ++h) {
+    float f[4];
+    unpack<TI>(x[h], f);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[4 * h + e] = v + h < c1 ? terms(f[e], ck) : 0.0;
   }
 }
 
-// One draw by one wavefront (the result is wave-uniform): the first element
-// whose cumulative mass exceeds t = u * S.
-template <class TI>
-__device__ int64_t smp_draw(const SmpLds& c, const void* zrow, uint32_t nvec, int tail,
-                            uint32_t CV, uint32_t nchunk, uint32_t C, double t, double S,
-                            double Md) {
+// Where a draw falls: chunk q and what is left of t there, in the row's scale.
+// pick says how the element is found: the crossing, or, where rounding left no
+// crossing, the first or last element of mass.  (All wave-uniform.)
+struct DrawAt {
+  int64_t q;
+  double r;
+  int pick;
+};
+template <int T, class Lds>
+__device__ __forceinline__ DrawAt smp_locate(const Lds& c, uint32_t nchunk, uint32_t C, double t,
+                                             double S) {
+  constexpr int PL = T / 64;  // run prefixes per lane
   const int lane = threadIdx.x & 63;
-  int64_t q = -1;
-  double r = 0.0;
-  int pick = kLast;
+  DrawAt d{-1, 0.0, kLast};
   if (t < S) {
-    // run: the first i with p[i] > t (each lane looks at 4 entries)
+    // run: the first i with p[i] > t (each lane looks at PL entries)
     int li = -1;
 #pragma unroll
-    for (int k = 3; k >= 0; --k)
-      if (c.p[4 * lane + k] > t) li = 4 * lane + k;
+    for (int k = PL - 1; k >= 0; --k)
+      if (c.p[PL * lane + k] > t) li = PL * lane + k;
     const int fl = first_lane(__ballot(li >= 0));
-    const int i = __shfl(li, fl < 0 ? 0 : fl, 64);  // fl >= 0: p[255] = S > t
-    r = fmax(t - (i ? c.p[i - 1] : 0.0), 0.0);
+    const int i = __builtin_amdgcn_readlane(li, fl < 0 ? 0 : fl);  // fl >= 0: p[T - 1] = S > t
+    d.r = fmax(t - (i ? c.p[i - 1] : 0.0), 0.0);
+    if (C == 1 && c.s[i] > 0.0) {  // a run is one chunk
+      d.q = i;
+      d.pick = kCross;
+      return d;
+    }
     // chunk within the run (C <= 8 chunks, one per lane)
     const uint32_t r0 = min((uint32_t)i * C, nchunk), r1 = min(r0 + C, nchunk);
     const uint32_t qq = r0 + (uint32_t)lane;
     const double sq = qq < r1 ? c.s[qq] : 0.0;
     const double incl = wave_incl_scan_f64(sq);
-    const int cl = first_lane(__ballot(qq < r1 && incl > r));
+    const int cl = first_lane(__ballot(qq < r1 && incl > d.r));
     if (cl >= 0) {
-      const double before = cl > 0 ? __shfl(incl, cl - 1, 64) : 0.0;
-      q = r0 + cl;
-      r = fmax(r - before, 0.0);
-      pick = kCross;
+      const double before = cl > 0 ? from_lane(incl, cl - 1) : 0.0;
+      d.q = r0 + cl;
+      d.r = fmax(d.r - before, 0.0);
+      d.pick = kCross;
     } else {
       const int ll = last_lane(__ballot(qq < r1 && sq > 0.0));
       if (ll >= 0) {
-        q = r0 + ll;
+        d.q = r0 + ll;
       } else {
-        q = chunk_positive(c, r1, nchunk, false);
-        pick = kFirst;
-        if (q < 0) {
-          q = chunk_positive(c, 0, r0, true);
-          pick = kLast;
+        d.q = chunk_positive(c.s, r1, nchunk, false);
+        d.pick = kFirst;
+        if (d.q < 0) {
+          d.q = chunk_positive(c.s, 0, r0, true);
+          d.pick = kLast;
         }
       }
     }
   } else {
-    q = chunk_positive(c, 0, nchunk, true);
+    d.q = chunk_positive(c.s, 0, nchunk, true);
   }
-  if (q < 0) return -1;  // no chunk of positive mass (excluded by S > 0)
+  return d;
+}
+
+// The element of a 128-vector step at which the mass acc (of the chunk's
+// earlier steps, unscaled) plus the step's, times fq, first exceeds r: its
+// offset in the step, -2 if rounding hides it in its lane, -1 if the step ends
+// below r (acc is then the mass so far).
+__device__ __forceinline__ int step_crossing(const double (&w)[8], double r, double fq,
+                                             double& acc) {
+  double lsum = 0.0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) lsum += w[e];
+  const double incl = acc + wave_incl_scan_f64(lsum);
+  const int vl = first_lane(__ballot(incl * fq > r));
+  if (vl < 0) {
+    acc = from_lane(incl, 63);
+    return -1;
+  }
+  double cum = vl > 0 ? from_lane(incl, vl - 1) : acc;
+  int ec = -1;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    cum += w[e];
+    if (ec < 0 && cum * fq > r) ec = e;
+  }
+  const int el = __builtin_amdgcn_readlane(ec, vl);
+  return el >= 0 ? 8 * vl + el : -2;
+}
+
+// The element of a draw (wave-uniform): the first whose cumulative mass
+// exceeds t = u * S.
+template <class TI, class Terms>
+__device__ __forceinline__ int64_t smp_element(DrawAt d, const Terms& terms, const void* zrow, uint32_t nvec,
+                               int tail, uint32_t CV) {
+  if (d.q < 0) return -1;  // no chunk of positive mass (excluded by S > 0)
   // element within chunk q, in steps of 128 vectors: lane l holds vectors
   // 2l and 2l + 1 of the step (elements 8l .. 8l + 7, in index order)
-  const float mq = c.m[q];
-  const double fq = exp_neg((double)mq - Md, c.tab);
-  const uint32_t c0 = (uint32_t)q * CV, c1 = min(c0 + CV, nvec);
-  if (pick == kCross) {
+  const typename Terms::Chunk ck = terms.chunk(d.q);
+  const uint32_t c0 = (uint32_t)d.q * CV, c1 = min(c0 + CV, nvec);
+  if (d.pick == kCross) {
     double acc = 0.0;  // unscaled mass of the earlier steps
     for (uint32_t v0 = c0; v0 < c1; v0 += kSmpStepVecs) {
+      typename TI::Vec x[2];
       double w[8];
-      step_terms<TI>(zrow, v0, c1, nvec, tail, mq, c.tab, w);
-      double lsum = 0.0;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) lsum += w[e];
-      const double incl = acc + wave_incl_scan_f64(lsum);
-      const int vl = first_lane(__ballot(incl * fq > r));
-      if (vl >= 0) {
-        double cum = vl > 0 ? __shfl(incl, vl - 1, 64) : acc;
-        int ec = -1;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          cum += w[e];
-          if (ec < 0 && cum * fq > r) ec = e;
-        }
-        const int el = __shfl(ec, vl, 64);
-        if (el >= 0) return ((int64_t)v0 + 2 * vl) * 4 + el;
-        break;  // rounding: no element crossing in that lane
-      }
-      acc = __shfl(incl, 63, 64);
+      step_load<TI>(zrow, v0, c1, nvec, tail, x);
+      step_terms<TI>(x, v0, c1, terms, ck, w);
+      const int at = step_crossing(w, d.r, ck.scale, acc);
+      if (at >= 0) return (int64_t)v0 * 4 + at;
+      if (at == -2) break;
     }
-    pick = kLast;  // rounding left no crossing: the last entry of mass
+    d.pick = kLast;  // rounding left no crossing: the last entry of mass
   }
   // first (or last) element of positive mass in the chunk
-  const bool last = pick == kLast;
+  const bool last = d.pick == kLast;
   const uint32_t nsteps = (c1 - c0 + kSmpStepVecs - 1) / kSmpStepVecs;
   for (uint32_t k = 0; k < nsteps; ++k) {
     const uint32_t v0 = c0 + (last ? nsteps - 1 - k : k) * kSmpStepVecs;
+    typename TI::Vec x[2];
     double w[8];
-    step_terms<TI>(zrow, v0, c1, nvec, tail, mq, c.tab, w);
+    step_load<TI>(zrow, v0, c1, nvec, tail, x);
+    step_terms<TI>(x, v0, c1, terms, ck, w);
     int ef = -1, eb = -1;
 #pragma unroll
     for (int e = 0; e < 8; ++e)
@@ -429,7 +507,7 @@ __device__ int64_t smp_draw(const SmpLds& c, const void* zrow, uint32_t nvec, in
         eb = e;
       }
     const int vl = last ? last_lane(__ballot(eb >= 0)) : first_lane(__ballot(ef >= 0));
-    if (vl >= 0) return ((int64_t)v0 + 2 * vl) * 4 + __shfl(last ? eb : ef, vl, 64);
+    if (vl >= 0) return ((int64_t)v0 + 2 * vl) * 4 + __builtin_amdgcn_readlane(last ? eb : ef, vl);
   }
   return -1;
 }
@@ -534,56 +612,40 @@ __device__ __forceinline__ void chunk_record(const void* zrow, uint32_t q, uint3
   sq_out = mq < __builtin_huge_valf() ? sum : __builtin_nan("");  // NaN or +inf max: NaN
 }
 
-template <class TI, bool WIDE>
-__global__ void __launch_bounds__(kSmpThreads) k_sample(CacheArgs a) {
-  constexpr int T = kSmpThreads, W = kSmpWaves;
-  __shared__ SmpLds c;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int64_t row = xcd_remap(blockIdx.x, gridDim.x);
+// The outputs of a masked row (tid of T lanes).
+template <int T>
+__device__ __forceinline__ void sample_masked_row(const CacheArgs& a, int64_t row) {
   const int M = a.K;
-  if (a.mask && a.mask[row] == 0) {
-    for (int i = tid; i < M; i += T) {
-      a.ids_out[row * M + i] = 0;
-      if (a.logp) a.logp[row * M + i] = 0.f;
-    }
-    if (tid == 0 && a.lse_out) a.lse_out[row] = 0.f;
-    return;
+  for (int i = threadIdx.x; i < M; i += T) {
+    a.ids_out[row * M + i] = 0;
+    if (a.logp) a.logp[row * M + i] = 0.f;
   }
-  for (int j = tid; j < kExpTab; j += kSmpThreads) c.tab[j] = exp2((double)j / kExpTab);
-  __syncthreads();
-  const void* zrow = (const char*)a.logits + row * a.ld * TI::BYTES;
-  const uint32_t nvec = (uint32_t)a.nvec;
-  const uint32_t steps = (nvec + kSmpStepVecs - 1) / kSmpStepVecs;
-  const uint32_t G = (steps + kSmpMaxChunks - 1) / kSmpMaxChunks;  // steps per chunk
-  const uint32_t CV = G * kSmpStepVecs;
-  const uint32_t nchunk = (nvec + CV - 1) / CV;  // <= kSmpMaxChunks
+  if (threadIdx.x == 0 && a.lse_out) a.lse_out[row] = 0.f;
+}
 
-  // one pass over the row: DPP row k of wave w takes chunks 4 w + k,
-  // 4 w + k + 4 W, ...
-  const uint32_t rowk = (uint32_t)lane >> 4, rl = (uint32_t)lane & 15;
-  float lmax = kNegInf;
-  for (uint32_t q0 = 4u * w; q0 < nchunk; q0 += 4u * W) {  // wave-uniform
-    const uint32_t q = q0 + rowk;
-    float mq;
-    double sq;
-    chunk_record<TI, WIDE>(zrow, q, q0, CV, nvec, a.tail, c.tab, mq, sq);
-    if (rl == 15 && q < nchunk) {
-      c.m[q] = mq;
-      c.s[q] = sq;
-    }
-    if (q < nchunk) lmax = max_nan(lmax, mq);
-  }
-  const float Mx = block_max<W>(lmax, c.red);  // ends with a barrier: records visible
-  const double Md = (double)Mx;
+// From the records of a row (visible to the workgroup) to its draws.  Md is
+// the maximum that the terms are relative to.
+template <class TI, int T, class Terms, class Lds>
+__device__ __forceinline__ void sample_finish(const CacheArgs& a, int64_t row, const void* zrow,
+                                              Lds& c, const Terms& terms, uint32_t CV,
+                                              uint32_t nchunk, double Md) {
+  constexpr int W = T / 64;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int M = a.K;
+  const uint32_t nvec = (uint32_t)a.nvec;
+  // wave w takes draws w, w + W, ... (at most 64: OPD_K_MAX / W), whose
+  // uniforms are requested here, ahead of their use
+  static_assert(kKMax <= 64 * W, "a wave's draws fit its lanes");
+  const int mine = w + lane * W;
+  const float my_u = mine < M ? a.u[row * M + mine] : 0.f;
   // records at the row max; runs of C consecutive chunks per thread
   const uint32_t C = (nchunk + T - 1) / T;
   {
     const uint32_t r0 = min((uint32_t)tid * C, nchunk), r1 = min(r0 + C, nchunk);
     double run = 0.0;
     for (uint32_t q = r0; q < r1; ++q) {
-      const float mq = c.m[q];
-      const double sq = mq == kNegInf ? 0.0 : c.s[q] * exp_neg((double)mq - Md, c.tab);
-      // (a NaN record keeps S NaN: the row has no distribution)
+      const double sq = terms.record(q, c.s[q]);
       c.s[q] = sq;
       run += sq;
     }
@@ -603,20 +665,523 @@ __global__ void __launch_bounds__(kSmpThreads) k_sample(CacheArgs a) {
   if (tid == 0 && a.lse_out) a.lse_out[row] = (float)L;
   // a NaN or +inf logit, or a row of -inf, leaves S NaN or 0: no distribution
   const bool defined = S > 0.0 && S <= 1.7976931348623157e308;
-  for (int i = w; i < M; i += W) {  // one draw per wavefront
-    const float u = a.u[row * M + i];
-    int32_t id = -1;
-    float lp = __builtin_nanf("");
-    if (defined && u >= 0.f && u < 1.f) {
-      const int64_t j = smp_draw<TI>(c, zrow, nvec, a.tail, CV, nchunk, C, (double)u * S, S, Md);
-      if (j >= 0) {
-        id = (int32_t)j;
-        lp = (float)((double)load_elem<TI>(zrow, j) - L);
+  // one draw per wavefront at a time, the next one's chunk located and on its
+  // way meanwhile; lane k keeps the wave's k-th draw
+  int32_t my_id = -1;
+  typename TI::Vec x[2], nx[2];
+  auto locate = [&](int k, typename TI::Vec (&v)[2]) {
+    DrawAt d{-1, 0.0, kLast};
+    const float u = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_u), k));
+    if (w + k * W < M && defined && u >= 0.f && u < 1.f)
+      d = smp_locate<T>(c, nchunk, C, (double)u * S, S);
+    if (d.q >= 0) {
+      const uint32_t c0 = (uint32_t)d.q * CV;
+      step_load<TI>(zrow, c0, min(c0 + CV, nvec), nvec, a.tail, v);
+    }
+    return d;
+  };
+  DrawAt d = locate(0, x);
+#pragma unroll 1
+  for (int k = 0; w + k * W < M; ++k) {
+    DrawAt nd{-1, 0.0, kLast};
+    if (k < 63) nd = locate(k + 1, nx);
+    if (d.q >= 0) {
+      int64_t id = -1;
+      const uint32_t c0 = (uint32_t)d.q * CV;
+      if (d.pick == kCross && CV == kSmpStepVecs) {
+        const typename Terms::Chunk ck = terms.chunk(d.q);
+        double wt[8], acc = 0.0;
+        step_terms<TI>(x, c0, min(c0 + CV, nvec), terms, ck, wt);
+        const int at = step_crossing(wt, d.r, ck.scale, acc);
+        if (at >= 0) id = (int64_t)c0 * 4 + at;
+      }
+      if (id < 0) id = smp_element<TI>(d, terms, zrow, nvec, a.tail, CV);
+      if (lane == k) my_id = (int32_t)id;
+    }
+    d = nd;
+    x[0] = nx[0];
+    x[1] = nx[1];
+  }
+  if (mine < M) {
+    a.ids_out[row * M + mine] = my_id;
+    if (a.logp)
+      a.logp[row * M + mine] =
+          my_id >= 0 ? (float)((double)load_elem<TI>(zrow, my_id) - L) : __builtin_nanf("");
+  }
+}
+
+// One row by T lanes, from the double-precision exponential (c.tab is set).
+template <class TI, bool WIDE, int T, int MAXC>
+__device__ __forceinline__ void sample_row(const CacheArgs& a, int64_t row, const void* zrow,
+                                           SmpLds<T, MAXC>& c) {
+  constexpr int W = T / 64;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const uint32_t nvec = (uint32_t)a.nvec;
+  const uint32_t steps = (nvec + kSmpStepVecs - 1) / kSmpStepVecs;
+  const uint32_t G = WIDE ? (steps + MAXC - 1) / MAXC : 1;  // steps per chunk
+  const uint32_t CV = G * kSmpStepVecs;
+  const uint32_t nchunk = (nvec + CV - 1) / CV;  // <= MAXC
+
+  // one pass over the row: DPP row k of wave w takes chunks 4 w + k,
+  // 4 w + k + 4 W, ...
+  const uint32_t rowk = (uint32_t)lane >> 4, rl = (uint32_t)lane & 15;
+  float lmax = kNegInf;
+  for (uint32_t q0 = 4u * w; q0 < nchunk; q0 += 4u * W) {  // wave-uniform
+    const uint32_t q = q0 + rowk;
+    float mq;
+    double sq;
+    chunk_record<TI, WIDE>(zrow, q, q0, CV, nvec, a.tail, c.tab, mq, sq);
+    if (rl == 15 && q < nchunk) {
+      c.m[q] = mq;
+      c.s[q] = sq;
+    }
+    if (q < nchunk) lmax = max_nan(lmax, mq);
+  }
+  const float Mx = block_max<W>(lmax, c.red);  // ends with a barrier: records visible
+  const double Md = (double)Mx;
+  sample_finish<TI, T>(a, row, zrow, c, ExpTerms{c.m, c.tab, Md}, CV, nchunk, Md);
+}
+
+template <class TI, bool WIDE>
+__global__ void __launch_bounds__(kSmpThreads) k_sample(CacheArgs a) {
+  __shared__ SmpLds<kSmpThreads, kSmpMaxChunks> c;
+  const int64_t row = xcd_remap(blockIdx.x, gridDim.x);
+  if (a.mask && a.mask[row] == 0) {
+    sample_masked_row<kSmpThreads>(a, row);
+    return;
+  }
+  for (int j = threadIdx.x; j < kExpTab; j += kSmpThreads) c.tab[j] = exp2((double)j / kExpTab);
+  __syncthreads();
+  sample_row<TI, WIDE>(a, row, (const char*)a.logits + row * a.ld * TI::BYTES, c);
+}
+
+// ---------------------------------------------------------------- draws of bf16 rows
+// A bf16 logit has few values: 23 binades of magnitude [2^-17, 64), both
+// signs, are 5,888.  k_sample_tab keeps exp(z) of each, in double, in LDS, so
+// the term of an element is one LDS read, and the pass over the row one integer
+// sequence and one double addition per element where the exponential takes
+// sixteen double-precision instructions; and the terms exp(z), not exp(z -
+// max), need no maximum.  The entries are within about 3.4e-16 relative
+// (exp_reduced: 1.5e-15).  A tile that holds any other value is summed by
+// term_any: magnitudes below 2^-17 by exp's series, logits below -820 (-inf
+// among them) as 0.  A row with a NaN, a logit of 64 or more or one in [-820,
+// -64), or whose sum is below exp(-60), is marked for k_sample_redo.  In the
+// rows that stay every term that is not 0 is at least exp(-64), and the row's
+// maximum is above -72 (its sum is at most V exp(max)), so a logit below -820
+// is 0 in double's exp(z - max) as well.
+//
+// One 1,024-lane workgroup per CU stays for all its rows, so the table is set
+// up once, and its 16 waves take work from one queue: for each row its tiles
+// (four chunks, 2,048 elements), then the draws of the row before it, four to
+// an item.  No wave waits for another's phase: rows stream while the last
+// one's draws wait for memory.  Records and prefixes of the rows under way lie
+// in a ring of slots.  A wave only ever waits for items before its own in the
+// queue (a draw for its row's tiles, a tile for the draws of the row that held
+// its slot), all of them held by running waves, so every wait ends.
+// Measured at 4,096 rows of V = 151,936, 16 draws each: 222 us (5.6 TB/s; a
+// plain read of the rows takes 183), against 430-450 us for k_sample, and 258
+// us with a workgroup, and a table, per row.
+constexpr int kTabThreads = 1024;
+constexpr int kTabRing = 2560;                  // records in the ring
+constexpr int kTabMaxSlots = 8;
+constexpr int kTabMaxChunks = kTabRing / 2;     // rows up to 655,360 entries
+constexpr int64_t kTabMinVec = 4096;
+constexpr int kTabCus = 256;
+constexpr int kTabDraws = 4;                    // draws per item
+constexpr uint32_t kTabLoExp = 110;             // biased exponent of 2^-17
+constexpr uint32_t kTabHiExp = 133;             // and of 64
+constexpr uint32_t kTabBase = kTabLoExp << 7;   // bf16 magnitude bits of 2^-17
+constexpr uint32_t kTabSize = (kTabHiExp - kTabLoExp) * 256;
+static_assert(kTabSize * 8 <= 65536, "a table offset in bytes has 16 bits");
+constexpr float kTabTiny = 7.62939453125e-06f;  // 2^-17
+constexpr float kTabHuge = 64.f;
+constexpr float kTabZero = -820.f;
+constexpr double kTabMinSum = 8.75651076269652e-27;  // exp(-60)
+// ids_out[row * M] of a row left to k_sample_redo
+constexpr int32_t kSampleRedo = -2;
+
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+struct TabLds {
+  double e[kTabSize];  // exp(z), z's magnitude and sign bit (rotated to the lowest) as index
+  union {
+    struct {
+      double s[kTabRing];  // chunk sums
+      double p[kTabRing];  // their inclusive prefix
+    };
+    double lo[kTabSize / 8];  // the table's low factors, while it is set up
+  };
+  uint32_t next;                   // the queue: the next item
+  uint32_t done[kTabMaxSlots];     // tiles summed of the row in a slot
+  uint32_t drawn[kTabMaxSlots];    // draw items ended in a slot, over all its rows
+  uint32_t ready[kTabMaxSlots];    // 1 + the row whose prefix a slot holds
+  uint32_t general[kTabMaxSlots];  // 1 + the row of a slot that is left to k_sample_redo
+};
+
+// Sets up the table with one exponential for every five entries: a magnitude is
+// (1 + h / 8 + l / 128) 2^x, so exp(z) is the entry at l = 0 times exp(+-l 2^(x
+// - 7)).  Ends with a barrier.
+__device__ __forceinline__ void tab_setup(TabLds& t) {
+  constexpr uint32_t T = kTabThreads, kHi = kTabSize / 16, kLo = kTabSize / 8;
+  for (uint32_t j = threadIdx.x; j < kHi + kLo; j += T) {
+    const bool high = j < kHi;
+    // the high entries by (binade, h, sign), the low factors by (binade, l, sign)
+    const uint32_t i = high ? j : j - kHi, sign = i & 1u;
+    const uint32_t x = high ? i >> 4 : i >> 5;
+    const uint32_t bits = ((x + kTabLoExp) << 7) | (high ? ((i >> 1) & 7u) << 4 : 0u);
+    const float m = __uint_as_float(bits << 16);  // 2^x for a low factor
+    const double z = high ? (double)m : (double)m * ((double)((i >> 1) & 15u) / 128.0);
+    const double v = exp(sign ? -z : z);
+    if (high)
+      t.e[(x << 8) | (((i >> 1) & 7u) << 5) | sign] = v;
+    else
+      t.lo[i] = v;
+  }
+  __syncthreads();
+  for (uint32_t j = threadIdx.x; j < kTabSize; j += T) {
+    const uint32_t l = (j >> 1) & 15u;
+    if (l != 0u) t.e[j] = t.e[j & ~30u] * t.lo[((j >> 8) << 5) | (j & 31u)];
+  }
+  __syncthreads();
+}
+
+// Table offsets (in elements) of the two logits in a dword; kTabSize or more
+// for a value that the table does not hold.  (Kept opaque, so that the range
+// check and the reads share one copy.)
+__device__ __forceinline__ u16x2 tab_index(uint32_t x) {
+  const u16x2 h = __builtin_bit_cast(u16x2, x);
+  uint32_t t = __builtin_bit_cast(
+      uint32_t, (u16x2)(h * (uint16_t)2 + ((h >> 15) - (uint16_t)(2 * kTabBase))));
+  asm("" : "+v"(t));
+  return __builtin_bit_cast(u16x2, t);
+}
+
+// exp(z) of any logit of a row that stays.
+__device__ __forceinline__ double term_any(float z, const double* e) {
+  const uint32_t b = __float_as_uint(z) >> 16;
+  const uint32_t t = (((b << 1) | (b >> 15)) - 2 * kTabBase) & 0xFFFFu;
+  if (t < kTabSize) return e[t];
+  const double d = (double)z;
+  // the next term of the series, z^4 / 24, is below 1.5e-22
+  return fabsf(z) < kTabTiny ? fma(d, fma(d, fma(d, 1.0 / 6.0, 0.5), 1.0), 1.0) : 0.0;
+}
+
+struct TabTerms {
+  const double* e;
+  struct Chunk {
+    double scale;
+  };
+  __device__ __forceinline__ Chunk chunk(int64_t) const { return Chunk{1.0}; }
+  __device__ __forceinline__ double operator()(float z, const Chunk&) const {
+    return term_any(z, e);
+  }
+};
+
+// The terms of two vectors per lane, if the table holds those of the whole
+// wavefront (vectors outside the chunk read as -inf, which it does not).
+__device__ __forceinline__ bool tab_terms(const InBf16::Vec (&x)[2], const double* e,
+                                          double (&w)[8]) {
+  u16x2 t[4], top = {0, 0};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    t[k] = tab_index(x[k / 2][k & 1]);
+    top = __builtin_elementwise_max(top, t[k]);
+  }
+  if (__ballot(top[0] >= kTabSize || top[1] >= kTabSize) != 0) return false;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    w[2 * k] = e[t[k][0]];
+    w[2 * k + 1] = e[t[k][1]];
+  }
+  return true;
+}
+
+// LDS words that waves of the workgroup pass work by.  A wave's LDS operations
+// complete in order; the fences keep the compiler to that order and wait for
+// LDS only, so loads from memory stay in flight.
+__device__ __forceinline__ uint32_t lds_peek(const uint32_t* p) {
+  const uint32_t v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+__device__ __forceinline__ void lds_release() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+}
+__device__ __forceinline__ void lds_acquire() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// one addition per wave; the value before it
+__device__ __forceinline__ uint32_t lds_count(uint32_t* p) {
+  uint32_t v = 0;
+  if ((threadIdx.x & 63) == 0)
+    v = __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+__device__ __forceinline__ void lds_post(uint32_t* p, uint32_t v) {
+  if ((threadIdx.x & 63) == 0)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// (waits for a value, or for a count to reach one)
+__device__ __forceinline__ void lds_wait(const uint32_t* p, uint32_t v) {
+  while ((int32_t)(lds_peek(p) - v) < 0) __builtin_amdgcn_s_sleep(1);
+}
+
+__global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
+  typedef InBf16 TI;
+  typedef TI::Vec Vec;
+  constexpr int R = kSmpLoads;
+  __shared__ TabLds sh;
+  const int lane = threadIdx.x & 63;
+  const uint32_t rowk = (uint32_t)lane >> 4, rl = (uint32_t)lane & 15;
+  const uint32_t nvec = (uint32_t)a.nvec, N = (uint32_t)a.N, M = (uint32_t)a.K;
+  const uint32_t nchunk = (nvec + kSmpStepVecs - 1) / kSmpStepVecs;  // <= kTabMaxChunks
+  // tiles of four chunks; one that holds the row's end or a ragged last vector
+  // takes the path of unusual values
+  constexpr uint32_t TILE = 4 * kSmpStepVecs;
+  const uint32_t nclean = a.tail == TI::EPV ? nvec : nvec - 1;
+  const uint32_t ntile = (nvec + TILE - 1) / TILE, ndraw = (M + kTabDraws - 1) / kTabDraws;
+  const uint32_t slots = min((uint32_t)kTabMaxSlots, (uint32_t)kTabRing / nchunk);  // >= 2
+  // the workgroup's rows are b, b + G, ...; block j of its queue holds the
+  // tiles of its row j and the draws of its row j - 1
+  const uint32_t G = gridDim.x, b0 = blockIdx.x;
+  const uint32_t rows = (N - b0 + G - 1) / G, per = ntile + ndraw, items = (rows + 1) * per;
+  const uint32_t magic = 0xFFFFFFFFu / per + 1;  // i / per = mulhi(i, magic) for i per < 2^32
+
+  for (int i = threadIdx.x; i < 1 + 4 * kTabMaxSlots; i += kTabThreads) (&sh.next)[i] = 0u;
+  tab_setup(sh);
+
+  // (blocks of 64 rows to each XCD, as xcd_remap, with constant divisors)
+  auto row_of = [&](uint32_t j) -> int64_t {
+    const uint32_t i = b0 + j * G, q = i >> 3;
+    if (i >= (N & ~511u)) return (int64_t)i;
+    return (int64_t)(((q >> 6) << 9) + ((i & 7u) << 6) + (q & 63u));
+  };
+  auto row_ptr = [&](int64_t row) { return (const char*)a.logits + row * a.ld * TI::BYTES; };
+  auto valid = [&](int64_t row) { return !a.mask || a.mask[row] != 0; };
+
+  // The draws [4 k, 4 k + 4) of the workgroup's row j.
+  auto draws = [&](uint32_t j, uint32_t k) __attribute__((always_inline)) {
+    const uint32_t slot = j % slots, base = slot * nchunk;
+    const int64_t row = row_of(j);
+    const uint32_t m = k * kTabDraws + (uint32_t)lane;  // this lane's draw
+    const bool mine = lane < kTabDraws && m < M;
+    int32_t id = 0;
+    float lp = 0.f;
+    if (!valid(row)) {
+      if (k == 0 && lane == 0 && a.lse_out) a.lse_out[row] = 0.f;
+      // (a slot's draw items are counted in the order of its rows)
+      lds_wait(&sh.drawn[slot], j / slots * ndraw);
+    } else {
+      const char* zrow = row_ptr(row);
+      const float u = mine ? a.u[row * M + m] : -1.f;
+      lds_wait(&sh.ready[slot], j + 1);
+      lds_acquire();
+      const double* s = sh.s + base;
+      const double* p = sh.p + base;
+      const double S = p[nchunk - 1];
+      if (lds_peek(&sh.general[slot]) == j + 1 || !(S >= kTabMinSum)) {
+        if (k == 0 && lane == 0) a.ids_out[row * M] = kSampleRedo;
+        lds_release();
+        lds_count(&sh.drawn[slot]);
+        return;
+      }
+      const double L = log(S);
+      if (k == 0 && lane == 0 && a.lse_out) a.lse_out[row] = (float)L;
+      // each lane's chunk: p[lo - 1] <= t < p[hi] throughout, so a crossing is
+      // found even where rounding leaves p short of monotone
+      const bool ok = u >= 0.f && u < 1.f;
+      const double t = (double)u * S;
+      uint32_t lo = 0, hi = nchunk - 1;
+      while (__ballot(lo < hi) != 0) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (p[mid] > t) hi = mid;
+        else if (lo < hi) lo = mid + 1;
+      }
+      // (t < S, as u <= 1 - 2^-24)
+      const double r = fmax(t - (lo ? p[lo - 1] : 0.0), 0.0);
+      id = -1;
+      // the chunks of the item's draws, all on their way together
+      Vec x[kTabDraws][2];
+#pragma unroll
+      for (int d = 0; d < kTabDraws; ++d) {
+        const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)lo, d) * kSmpStepVecs;
+        step_load<TI>(zrow, c0, min(c0 + kSmpStepVecs, nvec), nvec, a.tail, x[d]);
+      }
+      const uint64_t oks = __ballot(ok);
+#pragma unroll
+      for (int d = 0; d < kTabDraws; ++d) {
+        if (((oks >> d) & 1ull) == 0) continue;
+        const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)lo, d);
+        const uint32_t c0 = q * kSmpStepVecs, c1 = min(c0 + kSmpStepVecs, nvec);
+        const double rd = from_lane(r, d);
+        double w[8], acc = 0.0;
+        if (!tab_terms(x[d], sh.e, w))
+          step_terms<TI>(x[d], c0, c1, TabTerms{sh.e}, TabTerms::Chunk{1.0}, w);
+        const int at = step_crossing(w, rd, 1.0, acc);
+        int64_t j_id = (int64_t)c0 * 4 + at;
+        if (at < 0) {
+          // rounding left no crossing: the chunk's last entry of mass, or that
+          // of the nearest chunk that has any
+          DrawAt da{(int64_t)q, rd, kLast};
+          if (!(s[q] > 0.0)) {
+            da.q = chunk_positive(s, q + 1, nchunk, false);
+            da.pick = kFirst;
+            if (da.q < 0) {
+              da.q = chunk_positive(s, 0, q, true);
+              da.pick = kLast;
+            }
+          }
+          j_id = smp_element<TI>(da, TabTerms{sh.e}, zrow, nvec, a.tail, kSmpStepVecs);
+        }
+        if (lane == d) id = (int32_t)j_id;
+      }
+      lp = mine && id >= 0 ? (float)((double)load_elem<TI>(zrow, id) - L) : __builtin_nanf("");
+      lds_release();
+    }
+    lds_count(&sh.drawn[slot]);
+    if (mine) {
+      a.ids_out[row * M + m] = id;
+      if (a.logp) a.logp[row * M + m] = lp;
+    }
+  };
+
+  const uint32_t loff = (rowk * kSmpStepVecs + rl) * (uint32_t)sizeof(Vec);
+  Vec x[R];
+  bool have = false;        // a tile is in x (or on its way there)
+  uint32_t tj = 0, tk = 0;  // its row and its place there
+#pragma unroll 1
+  for (;;) {
+    u16x2 t[2 * R], top = {0, 0};
+    if (have) {
+#pragma unroll
+      for (int i = 0; i < 2 * R; ++i) {
+        t[i] = tab_index(x[i / 2][i & 1]);
+        top = __builtin_elementwise_max(top, t[i]);
       }
     }
-    if (lane == 0) {
-      a.ids_out[row * M + i] = id;
-      if (a.logp) a.logp[row * M + i] = lp;
+    // the next item; a tile's loads are issued before the current one is
+    // summed, and take its registers.  (Draws are left until it has been: they
+    // may wait for it.)
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t item = lds_count(&sh.next);
+    const uint32_t nj = __umulhi(item, magic), nk = item - nj * per;
+    const bool end = item >= items, draw = !end && nk >= ntile && nj > 0;
+    const bool tile = !end && nk < ntile && nj < rows && valid(row_of(nj));
+    if (tile) {
+      const Rsrc r = slot_rsrc(row_ptr(row_of(nj)), nvec * (uint32_t)sizeof(Vec),
+                               nk * TILE * (uint32_t)sizeof(Vec));
+#pragma unroll
+      for (int b = 0; b < R; ++b)
+        x[b] = buf_ld<TI, kAuxNt>(r, loff + 16u * (uint32_t)sizeof(Vec) * b);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (have) {
+      const uint32_t j = tj, k = tk, t0 = k * TILE, slot = j % slots;
+      double s0 = 0.0, s1 = 0.0;
+      if (t0 + TILE <= nclean &&
+          __ballot(top[0] >= kTabSize || top[1] >= kTabSize) == 0) {  // wave-uniform
+        // (eight reads in flight: the scheduling barriers keep each batch whole)
+#pragma unroll
+        for (int h = 0; h < 2 * R; h += 4) {
+          double v[8];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            // offsets in bytes, both in 16 bits
+            const uint32_t o = __builtin_bit_cast(uint32_t, (u16x2)(t[h + i] << 3));
+            v[2 * i] = *(const double*)((const char*)sh.e + (o & 0xFFFFu));
+            v[2 * i + 1] = *(const double*)((const char*)sh.e + (o >> 16));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            s0 += v[2 * i];
+            s1 += v[2 * i + 1];
+          }
+        }
+      } else {
+        // (from memory again: an index into x would put x there)
+        const char* zrow = row_ptr(row_of(j));
+        bool general = false;
+#pragma unroll 1
+        for (int b = 0; b < R; ++b) {
+          const uint32_t v = t0 + rowk * kSmpStepVecs + rl + 16u * b;
+          if (v >= nvec) break;
+          float f[4];
+          unpack<TI>(load_vec<TI>(zrow, v, nvec, a.tail), f);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            general |= !(f[e] < kTabHuge) || (f[e] < -kTabHuge && f[e] >= kTabZero);
+            s0 += term_any(f[e], sh.e);
+          }
+        }
+        if (__ballot(general) != 0) lds_post(&sh.general[slot], j + 1);
+      }
+      const double sum = row16_sum(s0 + s1);
+      // the slot's last row has been drawn from (see `draws`)
+      lds_wait(&sh.drawn[slot], j / slots * ndraw);
+      const uint32_t q = k * 4 + rowk;
+      if (rl == 15 && q < nchunk) sh.s[slot * nchunk + q] = sum;
+      lds_release();
+      if (lds_count(&sh.done[slot]) + 1 == ntile) {
+        // the row's last tile: its prefix, runs of C chunks per lane
+        lds_acquire();
+        const double* s = sh.s + slot * nchunk;
+        double* p = sh.p + slot * nchunk;
+        const uint32_t C = (nchunk + 63) / 64;
+        const uint32_t r0 = min((uint32_t)lane * C, nchunk), r1 = min(r0 + C, nchunk);
+        double run = 0.0;
+        for (uint32_t i = r0; i < r1; ++i) run += s[i];
+        double at = wave_incl_scan_f64(run) - run;
+        if (lane == 0) at = 0.0;
+        for (uint32_t i = r0; i < r1; ++i) {
+          at += s[i];
+          p[i] = at;
+        }
+        lds_post(&sh.done[slot], 0u);  // for the slot's next row, which waits for this one's draws
+        lds_release();
+        lds_post(&sh.ready[slot], j + 1);
+      }
+    }
+    if (draw) {
+      draws(nj - 1, nk - ntile);
+      // vmcnt(0): left to the compiler, the loads of a draw that was skipped
+      // would be waited for, and the next tile's with them, where their
+      // registers are used again in the sums
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+    }
+    if (end) break;
+    have = tile;
+    tj = nj;
+    tk = nk;
+  }
+}
+
+// The rows that k_sample_tab left, one workgroup taking every gridDim.x-th; the
+// usual case, none, costs a short grid that reads the marks.
+constexpr int kSampleRedoGroups = 512;
+__global__ void __launch_bounds__(kSmpThreads) k_sample_redo(CacheArgs a) {
+  __shared__ SmpLds<kSmpThreads, kSmpMaxChunks> c;
+  __shared__ uint32_t s_n;
+  __shared__ int64_t s_rows[kSmpThreads];
+  constexpr int T = kSmpThreads;
+  const int64_t stride = (int64_t)gridDim.x;
+  bool tab = false;
+  for (int64_t base = blockIdx.x; base < a.N; base += stride * T) {  // workgroup-uniform
+    if (threadIdx.x == 0) s_n = 0u;
+    __syncthreads();
+    const int64_t row = base + (int64_t)threadIdx.x * stride;
+    if (row < a.N && (!a.mask || a.mask[row] != 0) && a.ids_out[row * a.K] == kSampleRedo)
+      s_rows[atomicAdd(&s_n, 1u)] = row;
+    __syncthreads();
+    const uint32_t n = s_n;
+    if (n != 0 && !tab) {
+      for (int j = threadIdx.x; j < kExpTab; j += T) c.tab[j] = exp2((double)j / kExpTab);
+      tab = true;
+      __syncthreads();
+    }
+    for (uint32_t i = 0; i < n; ++i) {
+      sample_row<InBf16, false>(a, s_rows[i],
+                                (const char*)a.logits + s_rows[i] * a.ld * InBf16::BYTES, c);
+      __syncthreads();  // the next row's records wait for this row's draws
     }
   }
 }
@@ -1376,6 +1941,17 @@ hipError_t launch_op(const CacheArgs& a, CacheOp op, hipStream_t stream) {
 template <class TI>
 hipError_t launch_dt(const CacheArgs& a, CacheOp op, bool resident, hipStream_t stream) {
   if (op == CacheOp::Sample) {
+    if constexpr (TI::BYTES == 2) {
+      if (a.nvec >= kTabMinVec && a.nvec <= (int64_t)kTabMaxChunks * kSmpStepVecs) {
+        hipLaunchKernelGGL(k_sample_tab, dim3((unsigned)min(a.N, (int64_t)kTabCus)),
+                           dim3(kTabThreads), 0, stream, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_sample_redo, dim3((unsigned)min(a.N, (int64_t)kSampleRedoGroups)),
+                           dim3(kSmpThreads), 0, stream, a);
+        return hipGetLastError();
+      }
+    }
     // more than one 128-vector step per chunk above 2048 steps per row
     if ((a.nvec + kSmpStepVecs - 1) / kSmpStepVecs <= (int64_t)kSmpMaxChunks)
       hipLaunchKernelGGL((k_sample<TI, false>), dim3((unsigned)a.N), dim3(kSmpThreads), 0,

@@ -64,14 +64,16 @@ constexpr int kXcds = 8;
 #endif
 constexpr int64_t kXcdBlock = OPD_XCD_BLOCK;
 
-__device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t G) {
-  const int64_t B = G / kXcds < kXcdBlock ? G / kXcds : kXcdBlock;
+template <class I>
+__device__ __forceinline__ I xcd_remap_t(I b, I G) {
+  const I B = G / kXcds < (I)kXcdBlock ? G / kXcds : (I)kXcdBlock;
   if (B == 0) return b;
-  const int64_t span = B * kXcds;
+  const I span = B * kXcds;
   if (b >= G - G % span) return b;
-  const int64_t q = b / kXcds;  // b's place in its XCD's dispatch order
+  const I q = b / kXcds;  // b's place in its XCD's dispatch order
   return (q / B) * span + (b % kXcds) * B + q % B;
 }
+__device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t G) { return xcd_remap_t(b, G); }
 
 // One contiguous eighth of a one-shot grid per XCD (32-bit indices).  For
 // grids of short workgroups that each write one 16 KiB piece; measured on a

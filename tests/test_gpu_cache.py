@@ -213,6 +213,60 @@ def test_sample_stratified_uniforms_reproduce_the_distribution():
     assert np.all(np.abs(counts - n * p) <= 1)
 
 
+@pytest.mark.parametrize("V,ld,N,M", [
+    (16384, 16384, 1300, 5),     # the narrowest row of the table kernel; six rows to a workgroup
+    (16385, 16392, 700, 256),    # a last chunk of one element; the most draws
+    (131072, 131072, 20, 1),     # 256 records: eight slots still fit the ring
+    (655360, 655360, 4, 16),     # the widest row: two slots
+    (655361, 655368, 3, 16),     # one element more: the general kernel
+])
+def test_sample_table_rows(V, ld, N, M):
+    """The table kernel's queue (several rows to a workgroup, masked ones among
+    them) with rows of every kind: in the table's range, with magnitudes below
+    it (and zeros), with entries of no mass, and the kinds it leaves to the
+    general kernel (a logit of 64 or more, one in [-820, -64), undefined)."""
+    say("sample table V=%d N=%d M=%d" % (V, N, M))
+    rng = np.random.default_rng(V + M)
+    x = rng.normal(0.0, 3.0, (N, V)).astype(np.float32)
+    for r in range(0, N, 2):
+        at = rng.choice(V, 40, replace=False)
+        kind = r // 2 % 8
+        if kind == 0:
+            x[r, at] *= 1e-6
+            x[r, at[:5]] = [0.0, -0.0, 2.0 ** -17, -(2.0 ** -18), 1e-30]
+        elif kind == 1:
+            x[r, at] = [-np.inf, -3e38] * 20
+        elif kind == 2:
+            x[r, at[0]] = 64.0
+        elif kind == 3:
+            x[r, at[0]] = -64.5
+        elif kind == 4:
+            x[r, at[0]] = [np.nan, np.inf][r // 16 % 2]
+        elif kind == 5:
+            x[r] = -900.0  # no mass above exp(-820)
+        elif kind == 6:
+            x[r, at[0]] = 63.5
+            x[r, at[1]] = -63.5
+    stored = np.zeros((N, ld), np.uint16)
+    stored[:, :V] = to_stored(x, synth.BF16)
+    u = f32_uniforms(V + M, N, M)
+    u[:, 0] = 0.0
+    if M > 1:
+        u[:, 1] = np.nextafter(np.float32(1), np.float32(0))
+    mask = (rng.random(N) < 0.7).astype(np.uint8)
+    out = opd.sample_actions(as_device(stored, V), to_dev(u), mask=to_dev(mask), want_lse=True)
+    torch.cuda.synchronize()
+    ref = oracle.cache_rows("sample", synth.BF16, stored, V, M, uniforms=u, mask=mask)
+    ids, logp, lse = (out[k].cpu().numpy() for k in ("ids", "logp", "lse"))
+    keep = mask == 1
+    assert np.all(ids[~keep] == 0) and np.all(logp[~keep] == 0) and np.all(lse[~keep] == 0)
+    defined = keep & np.isfinite(ref["lse"])
+    assert np.all(ids[keep & ~defined] == -1)
+    check_draws("table", ids[defined], logp[defined], stored[defined], V, synth.BF16, u[defined],
+                {k: v[defined] for k, v in ref.items()})
+    assert np.all(np.abs(lse - ref["lse"])[defined] <= LP_TOL * (1 + np.abs(ref["lse"][defined])))
+
+
 @pytest.mark.slow
 def test_sample_full_size_mc16():
     w = synth.MC16
