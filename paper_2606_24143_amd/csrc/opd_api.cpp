@@ -202,31 +202,25 @@ bool row_fits(int64_t nvec, int32_t dtype) {
 
 // Workspace of opd_mc_diagnostics: regions in order, each 256-byte aligned.
 struct DiagLayout {
-  size_t rho, var, clip, vloc, ycol, savg, parts, hist, total;
-  int ncol;
-  int64_t nseq;
+  size_t rho, x, psum, parts, hist, total;
+  int64_t nseq, pieces;
 };
 
-DiagLayout diag_layout(int64_t N, int32_t M, const int32_t* groups, int32_t n_groups,
-                       int64_t seq_len) {
+DiagLayout diag_layout(int64_t N, int32_t M, int32_t n_groups, int64_t seq_len) {
   DiagLayout l{};
   auto take = [&](size_t bytes) {
     const size_t at = l.total;
     l.total += (bytes + 255) & ~(size_t)255;
     return at;
   };
-  l.ncol = M;
-  for (int k = 0; k < n_groups; ++k) l.ncol += M / groups[k];
   const bool seq = seq_len > 0 && n_groups > 0;
   l.nseq = seq ? (N + seq_len - 1) / seq_len : 0;
+  l.pieces = seq ? opd::diag_pieces(N, seq_len) : 0;
   l.rho = take((size_t)N * M * 4);
-  l.var = take((size_t)N * 4);
-  l.clip = take((size_t)N * 4);
-  l.vloc = take((size_t)N * (n_groups > 0 ? n_groups : 1) * 4);
-  l.ycol = seq ? take((size_t)N * l.ncol * 4) : 0;
-  l.savg = seq ? take((size_t)l.nseq * l.ncol * 4) : 0;
-  l.parts = take((size_t)opd::kDiagParts * (3 + opd::kDiagMaxGroups) * 8);
-  l.hist = take((4 * 256 + 4) * 4);
+  l.x = seq ? take((size_t)N * M * 4) : 0;
+  l.psum = seq ? take((size_t)(l.nseq * l.pieces) * (M + 1) * 8) : 0;
+  l.parts = take((size_t)opd::diag_parts(N) * (3 + opd::kDiagMaxGroups) * 8);
+  l.hist = take((size_t)opd::kDiagHistWords * 4);
   return l;
 }
 
@@ -478,7 +472,7 @@ int opd_score_actions(const void* logits, int32_t dtype, int64_t N, int64_t V, i
 size_t opd_mc_diag_workspace_bytes(int64_t N, int32_t M, const int32_t* group_sizes,
                                    int32_t n_groups, int64_t seq_len) {
   if (check_diag(N, M, 0.5f, 0.2f, group_sizes, n_groups, seq_len) != OPD_OK) return 0;
-  return diag_layout(N, M, group_sizes, n_groups, seq_len).total;
+  return diag_layout(N, M, n_groups, seq_len).total;
 }
 
 int opd_mc_diagnostics(const float* lse, const float* gathered, const float* teacher_logp,
@@ -491,7 +485,7 @@ int opd_mc_diagnostics(const float* lse, const float* gathered, const float* tea
   if (out->ratio_seq && (seq_len == 0 || n_groups == 0)) return OPD_ERR_PARAM;
   if (N == 0) return OPD_OK;
   if (!lse || !gathered || !teacher_logp || !behav_logp) return OPD_ERR_NULL;
-  const DiagLayout l = diag_layout(N, M, group_sizes, n_groups, seq_len);
+  const DiagLayout l = diag_layout(N, M, n_groups, seq_len);
   if (!workspace || workspace_bytes < l.total || !aligned16(workspace)) return OPD_ERR_WORKSPACE;
   opd::DiagArgs a{};
   a.lse = lse;
@@ -507,7 +501,7 @@ int opd_mc_diagnostics(const float* lse, const float* gathered, const float* tea
   for (int k = 0; k < n_groups; ++k) a.group[k] = group_sizes[k];
   a.seq_len = seq_len;
   a.nseq = l.nseq;
-  a.ncol = l.ncol;
+  a.pieces = l.pieces;
   a.row_mean = out->row_mean;
   a.row_var = out->row_var;
   a.row_rho_max = out->row_rho_max;
@@ -516,12 +510,9 @@ int opd_mc_diagnostics(const float* lse, const float* gathered, const float* tea
   a.ratio_local = out->ratio_local;
   a.ratio_seq = out->ratio_seq;
   char* ws = (char*)workspace;
-  a.ws_rho = (float*)(ws + l.rho);
-  a.ws_var = (float*)(ws + l.var);
-  a.ws_clip = (uint32_t*)(ws + l.clip);
-  a.ws_vloc = (float*)(ws + l.vloc);
-  a.ws_ycol = l.nseq ? (float*)(ws + l.ycol) : nullptr;
-  a.ws_savg = l.nseq ? (float*)(ws + l.savg) : nullptr;
+  a.ws_rho = (uint32_t*)(ws + l.rho);
+  a.ws_x = l.nseq && out->ratio_seq ? (float*)(ws + l.x) : nullptr;
+  a.ws_psum = a.ws_x ? (double*)(ws + l.psum) : nullptr;
   a.ws_parts = (double*)(ws + l.parts);
   a.ws_hist = (uint32_t*)(ws + l.hist);
   const hipError_t err = opd::launch_diag(a, (hipStream_t)stream);

@@ -6,19 +6,26 @@
 //   log p = z - L,  A = tau - log p,  rho = exp(log p - beta),  X = -rho A
 // give the statistics of Sec. 5.2 (the tail of rho_theta, Fig. 5) and App. E
 // (variance of the m-sample estimator at a fixed prefix and averaged over a
-// sequence, Table 6):
-//   rows     one wavefront per token: mean, unbiased variance and largest
-//            rho of its M terms; count of rho outside [1 - eps, 1 + eps];
-//            means of replicate groups of m draws and their variance
-//   seq      one wavefront per (sequence, replicate column): the column's
-//            average over the sequence's valid tokens
-//   select   the nearest-rank quantile of rho by radix selection over its
-//            bits (rho >= 0, so bits order like values): four 8-bit passes,
-//            each an integer histogram then a one-workgroup pick
-//   final    fixed-order sums in double (per-range parts, then one
-//            workgroup), the per-sequence set variances, the batch outputs
-// Integer histograms make the selection exact and order-independent; every
-// floating-point sum has a fixed order.
+// sequence, Table 6).  The data is a few megabytes, so launches and serial
+// chains are what costs; the calls run in five launches:
+//   zero     the quantile's histograms
+//   rows     4 to 64 lanes per token (as M needs): mean, unbiased variance and
+//            largest rho of its M terms; count of rho outside [1 - eps, 1 +
+//            eps]; means of replicate groups of m draws and their variance; the
+//            workgroup's parts of the batch sums; the histogram of the top 11
+//            bits of rho
+//   mid      the histogram of the next 11 bits within the bucket that holds the
+//            wanted rank; and, in workgroups of their own, sums of the X
+//            columns over pieces of the sequences
+//   low      the histogram of the last 10 bits
+//   final    the quantile; fixed-order sums of the parts in double; the
+//            per-sequence set variances; the batch outputs
+// rho >= 0, so its bits order like values.  Integer histograms make the
+// selection exact and order-independent; every floating-point sum has a fixed
+// order.  Measured (32,768 tokens, M = 16, three group sizes, 2,048-token
+// sequences): 38 us a call (rows 16, mid 5.5, low 5, final 10), against 116 in
+// thirteen launches with a launch each for the parts and each bucket's choice
+// and four passes of 8 bits.
 #include <math.h>
 
 #include "opd_device.h"
@@ -28,156 +35,217 @@ namespace {
 
 constexpr int kDiagThreads = 256;
 constexpr int kDiagWaves = kDiagThreads / 64;
+constexpr int kDiagQ = 3 + kDiagMaxGroups;
+// key of a masked token's entries: above every ratio's
+constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
 // Sort key of one ratio: its bits, with every NaN mapped above +inf.
 __device__ __forceinline__ uint32_t rho_key(float r) {
   return r != r ? 0x7FC00000u : __float_as_uint(r);
 }
 
-__device__ __forceinline__ float one_rho(const DiagArgs& a, int64_t t, int i, float L, float* X) {
-  const int64_t e = t * a.M + i;
-  const float lp = a.gathered[e] - L;
-  const float r = fast_exp2((lp - a.beta[e]) * kLog2e);
-  *X = -r * (a.tau[e] - lp);
-  return r;
+// The three digits of a key (top 11 of 32 bits, of which the first is 0; 11;
+// 10) and where their histograms start.
+constexpr int kBins0 = 1024, kBins1 = 2048, kBins2 = 1024;
+constexpr int kHist1 = kBins0, kHist2 = kBins0 + kBins1, kSel = kHist2 + kBins2;
+static_assert(kSel + 4 == kDiagHistWords, "the workspace holds the histograms and the state");
+constexpr int digit_bins(int pass) { return pass == 1 ? kBins1 : kBins0; }
+constexpr int digit_at(int pass) { return pass == 0 ? 0 : (pass == 1 ? kHist1 : kHist2); }
+__device__ __forceinline__ uint32_t digit(uint32_t key, int pass) {
+  return pass == 0 ? key >> 21 : (pass == 1 ? (key >> 10) & 2047u : key & 1023u);
 }
 
-__global__ void __launch_bounds__(kDiagThreads) k_diag_rows(DiagArgs a) {
-  __shared__ float s_x[kDiagWaves][kKMax];
+__global__ void __launch_bounds__(1024) k_diag_zero(DiagArgs a) {
+  for (int i = threadIdx.x; i < kDiagHistWords; i += 1024) a.ws_hist[i] = 0u;
+}
+
+// sums and maxima over the WIDTH lanes (a power of two) that share a token
+template <int WIDTH>
+__device__ __forceinline__ float sub_sum(float v) {
+#pragma unroll
+  for (int o = WIDTH >> 1; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+template <int WIDTH>
+__device__ __forceinline__ float sub_max(float v) {
+#pragma unroll
+  for (int o = WIDTH >> 1; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  return v;
+}
+
+// the sum over a wavefront, in lane 63 (DPP row shifts, then the row
+// broadcasts; lanes without a source add 0)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add_f64(double v) {
+  u32x2 h = __builtin_bit_cast(u32x2, v);
+  h[0] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h[0], CTRL, ROWS, 0xF, false);
+  h[1] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h[1], CTRL, ROWS, 0xF, false);
+  return v + __builtin_bit_cast(double, h);
+}
+__device__ __forceinline__ double wave_sum_f64(double v) {
+  v = dpp_add_f64<0x111, 0xF>(v);
+  v = dpp_add_f64<0x112, 0xF>(v);
+  v = dpp_add_f64<0x114, 0xF>(v);
+  v = dpp_add_f64<0x118, 0xF>(v);
+  v = dpp_add_f64<0x142, 0xA>(v);
+  return dpp_add_f64<0x143, 0xC>(v);
+}
+
+// Many waves, so that a wave does one or two rounds of its chain of loads and
+// reductions, and few workgroups, so that few histograms are merged.
+constexpr int kRowsThreads = 1024;
+constexpr int kRowsWaves = kRowsThreads / 64;
+
+// Workgroup b takes tokens [b per, (b + 1) per).  Quantities of the batch sums:
+// [0] sum of row_var, [1] clipped entries, [2] valid tokens, [3 + k] sum of the
+// group-k variances.
+template <int WIDTH>
+__global__ void __launch_bounds__(kRowsThreads, 8) k_diag_rows(DiagArgs a, int64_t per) {
+  constexpr int NG = WIDTH < 64 ? 1 : kKMax / 64;  // groups per lane at most
+  __shared__ float s_x[kRowsWaves][kKMax];
+  __shared__ uint32_t s_h[kBins0];
+  __shared__ double s_q[kRowsWaves][kDiagQ];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t t = (int64_t)blockIdx.x * kDiagWaves + w;
-  if (t >= a.N) return;
   const int M = a.M;
-  const bool valid = !a.mask || a.mask[t] != 0;
-  if (!valid) {
-    if (lane == 0) {
-      if (a.row_mean) a.row_mean[t] = 0.f;
-      if (a.row_var) a.row_var[t] = 0.f;
-      if (a.row_rho_max) a.row_rho_max[t] = 0.f;
+  constexpr int tpw = 64 / WIDTH;               // tokens per wave at a time
+  const int sub = lane / WIDTH, l = lane & (WIDTH - 1);
+  const int64_t t_end = min((int64_t)(blockIdx.x + 1) * per, a.N);
+  for (int i = threadIdx.x; i < kBins0; i += kRowsThreads) s_h[i] = 0u;
+  __syncthreads();
+  double q[kDiagQ];
+#pragma unroll
+  for (int i = 0; i < kDiagQ; ++i) q[i] = 0.0;
+  float* sx = &s_x[w][sub * M];  // (tpw > 1 only where M <= WIDTH)
+  for (int64_t tb = (int64_t)blockIdx.x * per + w * tpw; tb < t_end; tb += kRowsWaves * tpw) {
+    const int64_t t = tb + sub;
+    const bool in = t < t_end;
+    const bool valid = in && (!a.mask || a.mask[t] != 0);
+    const float L = valid ? a.lse[t] : 0.f;
+    float sum = 0.f, rmax = kNegInf, clip = 0.f;
+    for (int i = l; i < M; i += WIDTH) {
+      uint32_t key = kNoKey;
+      float X = 0.f;
+      if (valid) {
+        const int64_t e = t * M + i;
+        const float lp = a.gathered[e] - L;
+        const float r = fast_exp2((lp - a.beta[e]) * kLog2e);
+        X = -r * (a.tau[e] - lp);
+        key = rho_key(r);
+        if (a.rho_quantile) atomicAdd(&s_h[digit(key, 0)], 1u);
+        rmax = fmaxf(rmax, r);
+        clip += fabsf(r - 1.f) > a.clip_eps ? 1.f : 0.f;
+        sum += X;
+      }
+      if (in) {
+        if (a.rho_quantile) a.ws_rho[t * M + i] = key;
+        if (a.ws_x) a.ws_x[t * M + i] = X;
+      }
+      sx[i] = X;
     }
-    return;
-  }
-  const float L = a.lse[t];
-  float sum = 0.f, rmax = kNegInf;
-  uint32_t clip = 0;
-  for (int i = lane; i < M; i += 64) {
-    float X;
-    const float r = one_rho(a, t, i, L, &X);
-    a.ws_rho[t * M + i] = r;
-    s_x[w][i] = X;
-    sum += X;
-    rmax = fmaxf(rmax, r);
-    clip += fabsf(r - 1.f) > a.clip_eps ? 1u : 0u;
-  }
-  sum = wave_sum(sum);
-  rmax = wave_max(rmax);
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) clip += __shfl_xor(clip, o, 64);
-  const float mean = sum / (float)M;
-  float ss = 0.f;
-  for (int i = lane; i < M; i += 64) {
-    const float d = s_x[w][i] - mean;
-    ss += d * d;
-  }
-  ss = wave_sum(ss);
-  const float var = M >= 2 ? ss / (float)(M - 1) : __builtin_nanf("");
-  if (lane == 0) {
-    if (a.row_mean) a.row_mean[t] = mean;
-    if (a.row_var) a.row_var[t] = var;
-    if (a.row_rho_max) a.row_rho_max[t] = rmax == kNegInf ? __builtin_nanf("") : rmax;
-    a.ws_var[t] = var;
-    a.ws_clip[t] = clip;
-  }
-  // replicate groups of m consecutive draws (single draws first, for the
-  // sequence-level baseline)
-  float* ycol = a.ws_ycol ? a.ws_ycol + t * a.ncol : nullptr;
-  if (ycol)
-    for (int i = lane; i < M; i += 64) ycol[i] = s_x[w][i];
-  int col = M;
-  for (int k = 0; k < a.n_groups; ++k) {
-    const int m = a.group[k], G = M / m;
-    float ys = 0.f;
-    float y[4] = {0.f, 0.f, 0.f, 0.f};  // G <= 256: four groups per lane at most
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const int g = lane + 64 * h;
-      if (g < G) {
-        float acc = 0.f;
-        for (int i = g * m; i < g * m + m; ++i) acc += s_x[w][i];
-        y[h] = acc / (float)m;
-        ys += y[h];
-        if (ycol) ycol[col + g] = y[h];
+    // (each wave reads back only what it wrote)
+    __builtin_amdgcn_wave_barrier();
+    const float mean = sub_sum<WIDTH>(sum) / (float)M;
+    rmax = sub_max<WIDTH>(rmax);
+    clip = sub_sum<WIDTH>(clip);
+    float ss = 0.f;
+    for (int i = l; i < M; i += WIDTH) {
+      const float d = sx[i] - mean;
+      ss += d * d;
+    }
+    ss = sub_sum<WIDTH>(ss);
+    const float var = M >= 2 ? ss / (float)(M - 1) : __builtin_nanf("");
+    if (l == 0 && in) {
+      if (a.row_mean) a.row_mean[t] = valid ? mean : 0.f;
+      if (a.row_var) a.row_var[t] = valid ? var : 0.f;
+      if (a.row_rho_max)
+        a.row_rho_max[t] = !valid ? 0.f : (rmax == kNegInf ? __builtin_nanf("") : rmax);
+      if (valid) {
+        q[0] += M >= 2 ? (double)var : 0.0;
+        q[1] += (double)clip;
+        q[2] += 1.0;
       }
     }
-    const float ym = wave_sum(ys) / (float)G;
-    float yss = 0.f;
+    // replicate groups of m consecutive draws
+#pragma unroll 1
+    for (int k = 0; k < a.n_groups; ++k) {
+      const int m = a.group[k], G = M / m;
+      float ys = 0.f;
+      float y[NG];
 #pragma unroll
-    for (int h = 0; h < 4; ++h)
-      if (lane + 64 * h < G) yss += (y[h] - ym) * (y[h] - ym);
-    yss = wave_sum(yss);
-    if (lane == 0) a.ws_vloc[t * a.n_groups + k] = yss / (float)(G - 1);
-    col += G;
-  }
-}
-
-// One wavefront per (sequence, replicate column): the average of that column
-// over the sequence's valid tokens (lanes stride the tokens; fixed-order
-// butterfly sum).  The variances over the columns of each set are taken in
-// the final pass.
-__global__ void __launch_bounds__(kDiagThreads) k_diag_seq(DiagArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int c = blockIdx.y * kDiagWaves + (threadIdx.x >> 6);
-  if (c >= a.ncol) return;
-  const int64_t s = blockIdx.x;
-  const int64_t t0 = s * a.seq_len, t1 = min(t0 + a.seq_len, a.N);
-  float acc = 0.f;
-  uint32_t nv = 0;
-  for (int64_t t = t0 + lane; t < t1; t += 64) {
-    if (a.mask && a.mask[t] == 0) continue;
-    acc += a.ws_ycol[t * a.ncol + c];
-    ++nv;
-  }
-  acc = wave_sum(acc);
+      for (int h = 0; h < NG; ++h) {
+        const int g = l + WIDTH * h;
+        y[h] = 0.f;
+        if (g < G) {
+          float acc = 0.f;
+          for (int i = g * m; i < g * m + m; ++i) acc += sx[i];
+          y[h] = acc / (float)m;
+          ys += y[h];
+        }
+      }
+      const float ym = sub_sum<WIDTH>(ys) / (float)G;
+      float yss = 0.f;
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) nv += __shfl_xor(nv, o, 64);
-  if (lane == 0) a.ws_savg[s * a.ncol + c] = nv ? acc / (float)nv : __builtin_nanf("");
-}
-
-// The radix-select state lives in the workspace: sel[0] = key prefix chosen
-// so far, sel[1] = rank still to find within it, sel[2] = count of entries.
-__global__ void __launch_bounds__(kDiagThreads) k_diag_zero(DiagArgs a) {
-  for (int i = threadIdx.x; i < 4 * 256 + 4; i += kDiagThreads) a.ws_hist[i] = 0u;
-}
-
-__global__ void __launch_bounds__(kDiagThreads) k_diag_hist(DiagArgs a, int pass) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0u;
-  __syncthreads();
-  const uint32_t prefix = pass ? a.ws_hist[4 * 256 + 0] : 0u;
-  const int shift = 24 - 8 * pass;
-  const int64_t total = a.N * a.M;
-  for (int64_t e = (int64_t)blockIdx.x * kDiagThreads + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * kDiagThreads) {
-    const int64_t t = e / a.M;
-    if (a.mask && a.mask[t] == 0) continue;
-    const uint32_t key = rho_key(a.ws_rho[e]);
-    if (pass == 0 || (key >> (shift + 8)) == prefix) atomicAdd(&h[(key >> shift) & 255u], 1u);
+      for (int h = 0; h < NG; ++h)
+        if (l + WIDTH * h < G) yss += (y[h] - ym) * (y[h] - ym);
+      yss = sub_sum<WIDTH>(yss);
+      const double v = l == 0 && valid ? (double)(yss / (float)(G - 1)) : 0.0;
+#pragma unroll
+      for (int i = 0; i < kDiagMaxGroups; ++i)
+        if (i == k) q[3 + i] += v;
+    }
+    __builtin_amdgcn_wave_barrier();
   }
+  // the workgroup's parts, in a fixed order
+#pragma unroll
+  for (int i = 0; i < kDiagQ; ++i)
+    if (i < 3 + a.n_groups) {
+      const double v = wave_sum_f64(q[i]);
+      if (lane == 63) s_q[w][i] = v;
+    }
   __syncthreads();
-  if (h[threadIdx.x]) atomicAdd(&a.ws_hist[pass * 256 + threadIdx.x], h[threadIdx.x]);
+  if (threadIdx.x < 3 + a.n_groups) {
+    double v = 0.0;
+    for (int k = 0; k < kRowsWaves; ++k) v += s_q[k][threadIdx.x];
+    a.ws_parts[(int64_t)blockIdx.x * kDiagQ + threadIdx.x] = v;
+  }
+  if (a.rho_quantile)
+    for (int i = threadIdx.x; i < kBins0; i += kRowsThreads)
+      if (s_h[i]) atomicAdd(&a.ws_hist[i], s_h[i]);
 }
 
-// One workgroup of 256 lanes, one bucket each: an inclusive scan of the
-// counts finds the bucket holding the wanted rank.
-__global__ void __launch_bounds__(256) k_diag_pick(DiagArgs a, int pass) {
-  __shared__ uint32_t s_w[4];
-  __shared__ uint32_t s_rank;
-  uint32_t* sel = a.ws_hist + 4 * 256;
-  const uint32_t* hist = a.ws_hist + pass * 256;
-  const int b = threadIdx.x, lane = b & 63, w = b >> 6;
-  const uint32_t h = hist[b];
-  // inclusive scan of the counts (integers: any order gives the same sums)
-  uint32_t incl = h;
+// The bucket of a pass's histogram that holds the wanted rank, found by every
+// workgroup for itself (T lanes; an inclusive scan of the counts): the key
+// prefix so far, and the rank within it.  Pass 0 turns the quantile into a
+// rank.  `n` receives the count of entries (pass 0 only).  The state goes to
+// the workspace for the launches after (the same values from each workgroup).
+struct Picked {
+  uint32_t prefix, rank, n;
+};
+template <int T, int PASS>
+struct Pick {
+  static constexpr int kBins = digit_bins(PASS), kPer = (kBins + T - 1) / T;
+  uint32_t h[kPer];
+  // requests this lane's buckets
+  __device__ __forceinline__ void load(const DiagArgs& a) {
+    const uint32_t* hist = a.ws_hist + digit_at(PASS);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int b = (int)threadIdx.x * kPer + k;
+      h[k] = b < kBins ? hist[b] : 0u;
+    }
+  }
+  __device__ __forceinline__ Picked find(const DiagArgs& a, uint32_t prefix, uint32_t rank,
+                                         uint32_t* s_w, uint32_t* s_out) const;
+};
+template <int T, int PASS>
+__device__ __forceinline__ Picked Pick<T, PASS>::find(const DiagArgs& a, uint32_t prefix,
+                                                      uint32_t rank, uint32_t* s_w,
+                                                      uint32_t* s_out) const {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint32_t own = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) own += h[k];
+  uint32_t incl = own;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const uint32_t t = (uint32_t)__shfl_up((int)incl, o, 64);
@@ -185,116 +253,193 @@ __global__ void __launch_bounds__(256) k_diag_pick(DiagArgs a, int pass) {
   }
   if (lane == 63) s_w[w] = incl;
   __syncthreads();
-  for (int j = 0; j < w; ++j) incl += s_w[j];
-  const uint32_t n = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-  if (b == 0) {
-    if (pass == 0) {
-      sel[2] = n;
-      // nearest rank: the ceil(q n)-th smallest, at least the first
-      const double want = ceil((double)a.q * (double)n);
-      s_rank = n == 0 ? 1u : (uint32_t)(want < 1.0 ? 1.0 : (want > n ? (double)n : want));
-    } else {
-      s_rank = sel[1];
+  uint32_t n = 0;
+  for (int j = 0; j < T / 64; ++j) {
+    if (j < w) incl += s_w[j];
+    n += s_w[j];
+  }
+  if (PASS == 0) {
+    // nearest rank: the ceil(q n)-th smallest, at least the first
+    const double want = ceil((double)a.q * (double)n);
+    rank = n == 0 ? 1u : (uint32_t)(want < 1.0 ? 1.0 : (want > n ? (double)n : want));
+  }
+  // the one bucket with excl < rank <= incl (no entry: the last bucket)
+  uint32_t excl = incl - own;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int b = tid * kPer + k;
+    if (b < kBins &&
+        ((excl < rank && rank <= excl + h[k]) || (b == kBins - 1 && excl + h[k] < rank))) {
+      s_out[0] = prefix * (uint32_t)kBins + (uint32_t)b;
+      s_out[1] = rank - excl;
     }
+    excl += h[k];
   }
   __syncthreads();
-  const uint32_t rank = s_rank, excl = incl - h;
-  // the one bucket with excl < rank <= incl (the last one if rounding ever
-  // left rank beyond the total)
-  if ((excl < rank && rank <= incl) || (b == 255 && incl < rank)) {
-    const uint32_t prefix = pass == 0 ? 0u : sel[0];
-    sel[0] = (prefix << 8) | (uint32_t)b;
-    sel[1] = rank - excl;
-    if (pass == 3 && a.rho_quantile)
-      a.rho_quantile[0] = sel[2] == 0 ? __builtin_nanf("") : __uint_as_float((prefix << 8) | (uint32_t)b);
-  }
-}
-
-// Batch sums in two fixed-order stages: kDiagParts workgroups each sum a
-// contiguous range of tokens (lane-strided, then the lanes' partials in lane
-// order), in double; one workgroup then adds the parts in order and forms
-// the outputs.  Quantities: [0] sum of row_var, [1] clipped entries, [2]
-// valid tokens, [3 + k] sum of the group-k variances.
-__device__ __forceinline__ double block_sum_ordered(double v, double* red) {
-  red[threadIdx.x] = v;
+  const Picked r{s_out[0], s_out[1], n};
   __syncthreads();
-  double r = 0.0;
-  if (threadIdx.x == 0)
-    for (int j = 0; j < kDiagThreads; ++j) r += red[j];
-  __syncthreads();
-  return r;  // lane 0 only
+  return r;
 }
 
-__global__ void __launch_bounds__(kDiagThreads) k_diag_parts(DiagArgs a) {
-  __shared__ double red[kDiagThreads];
-  const int nq = 3 + a.n_groups;
-  const int64_t per = (a.N + kDiagParts - 1) / kDiagParts;
-  const int64_t t0 = blockIdx.x * per, t1 = min(t0 + per, a.N);
-  double* out = a.ws_parts + (int64_t)blockIdx.x * (3 + kDiagMaxGroups);
-  for (int q = 0; q < nq; ++q) {
-    double v = 0.0;
-    for (int64_t t = t0 + threadIdx.x; t < t1; t += kDiagThreads) {
-      if (a.mask && a.mask[t] == 0) continue;
-      if (q == 0)
-        v += a.M >= 2 ? (double)a.ws_var[t] : 0.0;
-      else if (q == 1)
-        v += (double)a.ws_clip[t];
-      else if (q == 2)
-        v += 1.0;
-      else
-        v += (double)a.ws_vloc[t * a.n_groups + (q - 3)];
-    }
-    v = block_sum_ordered(v, red);
-    if (threadIdx.x == 0) out[q] = v;
-  }
-}
-
-// Unbiased variance over the columns [c0, c0 + n) of one sequence.
-__device__ double seq_set_var(const float* avg, int c0, int n) {
-  double mean = 0.0;
-  for (int c = c0; c < c0 + n; ++c) mean += avg[c];
-  mean /= n;
-  double ss = 0.0;
-  for (int c = c0; c < c0 + n; ++c) ss += (avg[c] - mean) * (avg[c] - mean);
-  return ss / (n - 1);
-}
-
-__global__ void __launch_bounds__(kDiagThreads) k_diag_final(DiagArgs a) {
-  __shared__ double red[kDiagThreads];
-  __shared__ double tot[3 + kDiagMaxGroups];
-  __shared__ double seq[kDiagMaxGroups + 1];
+// The histogram of one of the later digits, over the keys whose earlier ones
+// are the picked bucket's; in pass 1, workgroups from hist_groups on sum one
+// piece of a sequence each.
+template <int PASS>
+__global__ void __launch_bounds__(kDiagThreads) k_diag_hist(DiagArgs a, unsigned hist_groups) {
+  __shared__ uint32_t h[digit_bins(PASS)];
+  __shared__ uint32_t s_w[kDiagWaves], s_out[2];
   const int tid = threadIdx.x;
-  if (tid < 3 + a.n_groups) {
-    double v = 0.0;
-    for (int p = 0; p < kDiagParts; ++p) v += a.ws_parts[p * (3 + kDiagMaxGroups) + tid];
-    tot[tid] = v;
-  }
-  // sequence level: set 0 = the M single-draw columns, set k >= 1 = the
-  // groups of size group[k - 1]; sequences without a valid token are skipped
-  if (a.ws_savg) {
-    for (int k = 0; k <= a.n_groups; ++k) {
-      int c0 = 0, n = a.M;
-      if (k > 0) {
-        c0 = a.M;
-        for (int j = 0; j < k - 1; ++j) c0 += a.M / a.group[j];
-        n = a.M / a.group[k - 1];
+  if (PASS == 1 && blockIdx.x >= hist_groups) {
+    // lanes as (token, column): c = tid % M of token tid / M
+    __shared__ double s_sum[kDiagThreads];
+    __shared__ uint32_t s_n[kDiagThreads];
+    const int64_t piece = blockIdx.x - hist_groups;
+    const int64_t s = piece / a.pieces, k = piece % a.pieces;
+    const int64_t t0 = s * a.seq_len + k * kDiagPiece;
+    const int64_t t1 = min(min(t0 + kDiagPiece, (s + 1) * a.seq_len), a.N);
+    const int M = a.M, R = kDiagThreads / M, tr = tid / M, c = tid - tr * M;
+    double acc = 0.0;
+    uint32_t nv = 0;
+    if (tr < R)
+#pragma unroll 4
+      for (int64_t t = t0 + tr; t < t1; t += R) {  // (a masked token's terms are 0)
+        acc += (double)a.ws_x[t * M + c];
+        nv += !a.mask || a.mask[t] != 0 ? 1u : 0u;
       }
+    s_sum[tid] = acc;
+    s_n[tid] = nv;
+    __syncthreads();
+    if (tid < M) {
       double v = 0.0;
-      for (int64_t s = tid; s < a.nseq; s += kDiagThreads) {
-        const float* avg = a.ws_savg + s * a.ncol;
-        if (avg[0] == avg[0]) v += seq_set_var(avg, c0, n);
+      uint32_t n = 0;
+      for (int j = 0; j < R; ++j) {
+        v += s_sum[j * M + tid];
+        n += s_n[j * M + tid];
       }
-      v = block_sum_ordered(v, red);
-      if (tid == 0) seq[k] = v;
+      a.ws_psum[piece * (M + 1) + tid] = v;
+      if (tid == 0) a.ws_psum[piece * (M + 1) + M] = (double)n;
     }
+    return;
+  }
+  Pick<kDiagThreads, PASS - 1> before;
+  before.load(a);
+  const Picked p = before.find(a, PASS == 1 ? 0u : a.ws_hist[kSel],
+                               PASS == 1 ? 0u : a.ws_hist[kSel + 1], s_w, s_out);
+  for (int i = tid; i < digit_bins(PASS); i += kDiagThreads) h[i] = 0u;
+  __syncthreads();
+  const uint32_t prefix = p.prefix;
+  auto count = [&](uint32_t key) {
+    if ((PASS == 1 ? key >> 21 : key >> 10) == prefix) atomicAdd(&h[digit(key, PASS)], 1u);
+  };
+  // (a masked token's key shares no prefix with a ratio's)
+  const int64_t total = a.N * a.M, quads = total / 4;
+  for (int64_t e = (int64_t)blockIdx.x * kDiagThreads + tid; e < quads;
+       e += (int64_t)hist_groups * kDiagThreads) {
+    const u32x4 v = ((const u32x4*)a.ws_rho)[e];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) count(v[k]);
+  }
+  if (blockIdx.x == 0 && tid < (int)(total - 4 * quads)) count(a.ws_rho[4 * quads + tid]);
+  __syncthreads();
+  for (int i = tid; i < digit_bins(PASS); i += kDiagThreads)
+    if (h[i]) atomicAdd(&a.ws_hist[digit_at(PASS) + i], h[i]);
+  // Pass 2 still reads its state here, so it leaves its own in other words.
+  if (blockIdx.x == 0 && tid == 0) {
+    a.ws_hist[kSel + (PASS == 1 ? 0 : 2)] = p.prefix;
+    a.ws_hist[kSel + (PASS == 1 ? 1 : 3)] = p.rank;
+  }
+}
+
+// One workgroup: the quantile, the batch sums, the sequence-level ratios.
+constexpr int kFinalThreads = 1024;
+constexpr int kFinalAvg = 2048;  // column averages of a batch of sequences
+
+__global__ void __launch_bounds__(kFinalThreads) k_diag_final(DiagArgs a, int parts) {
+  constexpr int T = kFinalThreads, W = T / 64;
+  __shared__ uint32_t s_w[W], s_out[2];
+  __shared__ double s_avg[kFinalAvg];
+  __shared__ double s_var[kFinalAvg];
+  static_assert(kDiagQ <= W, "a wave for each quantity");
+  __shared__ double tot[kDiagQ];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int M = a.M, sets = a.n_groups + 1;
+  // what every part below needs from memory is requested first: one round trip
+  Pick<T, 2> last;
+  uint32_t prefix = 0, rank = 0;
+  if (a.rho_quantile) {
+    last.load(a);
+    prefix = a.ws_hist[kSel + 2];
+    rank = a.ws_hist[kSel + 3];
+  }
+  // a column's average over the valid tokens of one sequence
+  auto average = [&](int64_t s, int c) {
+    const double* p = a.ws_psum + s * a.pieces * (M + 1);
+    double v = 0.0, n = 0.0;
+#pragma unroll 8
+    for (int64_t k = 0; k < a.pieces; ++k) {
+      v += p[k * (M + 1) + c];
+      n += p[k * (M + 1) + M];
+    }
+    return n > 0.0 ? v / n : __builtin_nan("");
+  };
+  const bool with_seq = a.ratio_seq && a.ws_psum;
+  const int64_t batch = kFinalAvg / (M > sets ? M : sets);
+  double avg0 = 0.0;  // this lane's column of the first batch
+  if (with_seq && tid < (int)min(batch, a.nseq) * M) avg0 = average(tid / M, tid % M);
+  // batch sums: wave i adds the parts of quantity i
+  if (w < 3 + a.n_groups) {
+    double v = 0.0;
+#pragma unroll 8
+    for (int p = lane; p < parts; p += 64) v += a.ws_parts[(int64_t)p * kDiagQ + w];
+    v = wave_sum_f64(v);
+    if (lane == 63) tot[w] = v;
   }
   __syncthreads();
+  if (a.rho_quantile) {
+    const Picked p = last.find(a, prefix, rank, s_w, s_out);
+    // (tot[2] valid tokens; none: no ratio)
+    if (tid == 0) a.rho_quantile[0] = tot[2] > 0.0 ? __uint_as_float(p.prefix) : __builtin_nanf("");
+  }
+  // sequence level: set 0 = the M single-draw columns, set k >= 1 = the means
+  // of group[k - 1] consecutive ones (a column's average over tokens commutes
+  // with the mean over draws); sequences without a valid token are skipped.
+  // Lane k < sets keeps set k's sum over the sequences, in order.
+  double seq = 0.0;
+  if (with_seq) {
+    for (int64_t s0 = 0; s0 < a.nseq; s0 += batch) {
+      const int ns = (int)min(batch, a.nseq - s0);
+      for (int i = tid; i < ns * M; i += T)
+        s_avg[i] = s0 == 0 && i == tid ? avg0 : average(s0 + i / M, i % M);
+      __syncthreads();
+      for (int i = tid; i < ns * sets; i += T) {
+        const int k = i % sets, m = k ? a.group[k - 1] : 1, n = M / m;
+        const double* avg = s_avg + (i / sets) * M;
+        double mean = 0.0;
+        for (int c = 0; c < n * m; ++c) mean += avg[c];
+        mean /= (double)(n * m);
+        double ss = 0.0;
+        for (int g = 0; g < n; ++g) {
+          double y = 0.0;
+          for (int c = g * m; c < g * m + m; ++c) y += avg[c];
+          y = y / m - mean;
+          ss += y * y;
+        }
+        s_var[i] = avg[0] == avg[0] ? ss / (n - 1) : 0.0;
+      }
+      __syncthreads();
+      if (tid < sets)
+        for (int s = 0; s < ns; ++s) seq += s_var[s * sets + tid];
+      __syncthreads();
+    }
+    if (tid < sets) s_avg[tid] = seq;
+    __syncthreads();
+  }
   if (tid == 0) {
-    const double n = tot[2] * (double)a.M;
+    const double n = tot[2] * (double)M;
     if (a.clip_frac) a.clip_frac[0] = n > 0 ? (float)(tot[1] / n) : __builtin_nanf("");
     for (int k = 0; k < a.n_groups; ++k) {
       if (a.ratio_local) a.ratio_local[k] = (float)(tot[3 + k] / tot[0]);
-      if (a.ratio_seq && a.ws_savg) a.ratio_seq[k] = (float)(seq[1 + k] / seq[0]);
+      if (with_seq) a.ratio_seq[k] = (float)(s_avg[1 + k] / s_avg[0]);
     }
   }
 }
@@ -304,23 +449,28 @@ __global__ void __launch_bounds__(kDiagThreads) k_diag_final(DiagArgs a) {
 hipError_t launch_diag(const DiagArgs& a, hipStream_t stream) {
   if (a.N == 0) return hipSuccess;
   const dim3 blk(kDiagThreads);
-  hipLaunchKernelGGL(k_diag_zero, dim3(1), blk, 0, stream, a);
-  hipLaunchKernelGGL(k_diag_rows, dim3((unsigned)((a.N + kDiagWaves - 1) / kDiagWaves)), blk, 0,
-                     stream, a);
-  if (a.ws_savg)
-    hipLaunchKernelGGL(k_diag_seq, dim3((unsigned)a.nseq, (unsigned)((a.ncol + kDiagWaves - 1) / kDiagWaves)),
-                       blk, 0, stream, a);
-  if (a.rho_quantile) {
-    const int64_t total = a.N * a.M;
-    const int64_t blocks = (total + kDiagThreads - 1) / kDiagThreads;
-    const unsigned grid = (unsigned)(blocks < 2048 ? blocks : 2048);
-    for (int pass = 0; pass < 4; ++pass) {
-      hipLaunchKernelGGL(k_diag_hist, dim3(grid), blk, 0, stream, a, pass);
-      hipLaunchKernelGGL(k_diag_pick, dim3(1), dim3(256), 0, stream, a, pass);
-    }
-  }
-  hipLaunchKernelGGL(k_diag_parts, dim3(kDiagParts), blk, 0, stream, a);
-  hipLaunchKernelGGL(k_diag_final, dim3(1), blk, 0, stream, a);
+  const int parts = diag_parts(a.N);
+  const int64_t per = (a.N + parts - 1) / parts;
+  if (a.rho_quantile) hipLaunchKernelGGL(k_diag_zero, dim3(1), dim3(1024), 0, stream, a);
+  // lanes per token: the power of two that holds its M entries, 64 at most
+  const dim3 rgrid((unsigned)parts), rblk(kRowsThreads);
+  if (a.M <= 4)
+    hipLaunchKernelGGL(k_diag_rows<4>, rgrid, rblk, 0, stream, a, per);
+  else if (a.M <= 8)
+    hipLaunchKernelGGL(k_diag_rows<8>, rgrid, rblk, 0, stream, a, per);
+  else if (a.M <= 16)
+    hipLaunchKernelGGL(k_diag_rows<16>, rgrid, rblk, 0, stream, a, per);
+  else if (a.M <= 32)
+    hipLaunchKernelGGL(k_diag_rows<32>, rgrid, rblk, 0, stream, a, per);
+  else
+    hipLaunchKernelGGL(k_diag_rows<64>, rgrid, rblk, 0, stream, a, per);
+  const int64_t quads = (a.N * a.M / 4 + kDiagThreads - 1) / kDiagThreads;
+  const unsigned groups = a.rho_quantile ? (unsigned)(quads < 1 ? 1 : (quads < 512 ? quads : 512)) : 0u;
+  const unsigned pieces = a.ws_psum ? (unsigned)(a.nseq * a.pieces) : 0u;
+  if (groups + pieces > 0)
+    hipLaunchKernelGGL(k_diag_hist<1>, dim3(groups + pieces), blk, 0, stream, a, groups);
+  if (a.rho_quantile) hipLaunchKernelGGL(k_diag_hist<2>, dim3(groups), blk, 0, stream, a, groups);
+  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kFinalThreads), 0, stream, a, parts);
   return hipGetLastError();
 }
 

@@ -93,8 +93,20 @@ hipError_t launch_cache(const CacheArgs& a, CacheOp op, int in_dt, bool resident
 
 // Monte-Carlo diagnostics (opd_mc_diagnostics).
 constexpr int kDiagMaxGroups = 8;
-// workgroups of the first stage of the batch sums
-constexpr int kDiagParts = 64;
+// workgroups of the rows launch (16 waves), each with its parts of the batch
+// sums: 16 tokens at least, two workgroups per CU at most
+constexpr int64_t kDiagMaxParts = 512;
+inline int diag_parts(int64_t N) {
+  const int64_t p = (N + 15) / 16;
+  return (int)(p < 1 ? 1 : (p < kDiagMaxParts ? p : kDiagMaxParts));
+}
+// quantile histograms of 10, 11 and 10 bits, and four words of state
+constexpr int kDiagHistWords = 1024 + 2048 + 1024 + 4;
+// pieces that a sequence's columns are summed in, a workgroup each
+constexpr int64_t kDiagPiece = 128;  // tokens
+inline int64_t diag_pieces(int64_t N, int64_t seq_len) {
+  return ((seq_len < N ? seq_len : N) + kDiagPiece - 1) / kDiagPiece;
+}
 
 struct DiagArgs {
   const float* lse;       // [N]
@@ -108,18 +120,15 @@ struct DiagArgs {
   int n_groups;
   int group[kDiagMaxGroups];
   int64_t seq_len, nseq;
-  int ncol;               // replicate columns per token
+  int64_t pieces;         // of a sequence (diag_pieces)
   // outputs (nullable)
   float *row_mean, *row_var, *row_rho_max, *rho_quantile, *clip_frac, *ratio_local, *ratio_seq;
   // workspace
-  float* ws_rho;          // [N, M]
-  float* ws_var;          // [N]
-  uint32_t* ws_clip;      // [N]
-  float* ws_vloc;         // [N, n_groups]
-  float* ws_ycol;         // [N, ncol] (sequence ratios only, else NULL)
-  float* ws_savg;         // [nseq, ncol] (sequence ratios only, else NULL)
-  double* ws_parts;       // [kDiagParts, 3 + kDiagMaxGroups] first-stage sums
-  uint32_t* ws_hist;      // [4 * 256 + 4] radix-select histograms and state
+  uint32_t* ws_rho;       // [N, M] sort keys of the ratios
+  float* ws_x;            // [N, M] one-sample terms (sequence ratios only, else NULL)
+  double* ws_psum;        // [nseq, pieces, M + 1] column sums and valid tokens (the same)
+  double* ws_parts;       // [diag_parts, 3 + kDiagMaxGroups] first-stage sums
+  uint32_t* ws_hist;      // [kDiagHistWords] radix-select histograms and state
 };
 
 hipError_t launch_diag(const DiagArgs& a, hipStream_t stream);

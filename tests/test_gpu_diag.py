@@ -91,6 +91,33 @@ def test_diag_parity(N, M, groups, seq, ragged, q):
         assert np.all(np.isnan(got["row_var"].cpu().numpy()))
 
 
+@pytest.mark.parametrize("N,M,groups,seq", [
+    (17, 2, (1,), 1),            # one token to a sequence; 16 tokens and one more
+    (700, 3, (1,), 129),         # one token past a piece of a sequence
+    (9000, 8, (1, 2, 4), 1000),  # more tokens than one round of every workgroup
+    (1100, 33, (3, 11), 257),    # odd sizes, a short last sequence
+    (520, 64, (2, 32), 128),     # the most draws with one entry to a lane
+    (300, 100, (1, 2, 4, 5, 10, 20, 25, 50), 300),  # the most group sizes
+])
+def test_diag_sizes(N, M, groups, seq):
+    """Lanes per token, pieces of sequences and parts of the batch at their
+    edges, on made-up log-probs with masked tokens."""
+    say("diag sizes N=%d M=%d groups=%s seq=%d" % (N, M, groups, seq))
+    rng = np.random.default_rng(N + M)
+    lse = (16 + rng.normal(0, 0.5, N)).astype(np.float32)
+    logp = -2 - 2.5 * np.abs(rng.normal(0, 1, (N, M)))
+    gathered = (logp + lse[:, None]).astype(np.float32)
+    tau = (logp + rng.normal(0, 1, (N, M))).astype(np.float32)
+    beta = (logp + rng.normal(0, 0.4, (N, M))).astype(np.float32)
+    mask = (rng.random(N) < 0.8).astype(np.uint8)
+    got = opd.mc_diagnostics(to_dev(lse), to_dev(gathered), to_dev(tau), to_dev(beta),
+                             mask=to_dev(mask), group_sizes=groups, seq_len=seq)
+    torch.cuda.synchronize()
+    ref = oracle.mc_diagnostics(lse, gathered, tau, beta, mask=mask, q=float(np.float32(0.99)),
+                                eps=float(np.float32(0.2)), group_sizes=groups, seq_len=seq)
+    compare(got, ref, tau, beta, lse, gathered, mask, float(np.float32(0.2)))
+
+
 def test_diag_is_deterministic():
     lse, gathered, tau, beta, mask = inputs(500, 16, ragged=True)
     args = (to_dev(lse), to_dev(gathered), to_dev(tau), to_dev(beta))
