@@ -850,68 +850,170 @@ __device__ __forceinline__ Stats lane_stats(const void* zrow, const void* yrow, 
   return s;
 }
 
-// One 1024-lane workgroup per row, streaming: sweep 1 reads the row(s),
-// sweep 2 reads them again (plain loads, so the second read can hit L2 or the
-// Infinity Cache).  For rows wider than the registers hold, and for the dense
-// estimators, which read two rows.
+// Rows wider than the registers hold (fp32 above 77,824 entries, bf16 above
+// 155,648), estimators with one row: as much of the row as fits is kept on
+// chip between the sweeps, kWideVgprs registers per lane and kYLdsBytes of LDS
+// (slots of kRowThreads vectors; 27 of 38 for fp32 rows of 151,936), and only
+// the rest is read a second time, with plain loads, which the Infinity Cache
+// can serve.  Sweep 1 requests the register slots, then streams the others
+// through an online (max, sum) while those are on their way.  HBM-bound: the
+// re-read is what is over the row's own bytes.  Measured against both sweeps
+// from memory, fp32 rows of 151,936: 1,024 rows with 64 draws 250 us against
+// 336, 4,096 with 16 906 against 1,325; bf16 rows of 300,000, 512 rows: 202
+// against 239.
+constexpr int kWideVgprs = 72;
+constexpr int kWideAhead = 4;
+
 template <class TI, class TO, int EST>
-__global__ void __launch_bounds__(kRowThreads) k_row_stream(Args a) {
-  constexpr int NT = kRowThreads, NW = NT / 64, EPV = TI::EPV;
-  constexpr bool DENSE = is_dense(EST);
+__global__ void __launch_bounds__(kRowThreads) k_row_wide(Args a) {
+  constexpr int NT = kRowThreads, NW = NT / 64, EPV = TI::EPV, B = kWideAhead;
+  typedef typename TI::Vec Vec;
+  constexpr uint32_t NR = kWideVgprs / (sizeof(Vec) / 4);         // slots in registers
+  constexpr uint32_t NL = kYLdsBytes / (NT * (uint32_t)sizeof(Vec));  // slots in LDS
+  static_assert(!is_dense(EST), "dense estimators read two rows");
+  __shared__ Vec s_z[is_mc(EST) ? NL : 1][NT];
   __shared__ Stats s_red[NW];
   __shared__ CacheLds c;
   const int tid = threadIdx.x;
   const int64_t row = xcd_remap(blockIdx.x, gridDim.x);
   const void* zrow = (const char*)a.logits + row * a.ld * TI::BYTES;
-  const void* yrow = DENSE ? (const char*)a.teacher + row * a.ld * TI::BYTES : nullptr;
   void* grow = (char*)a.dlogits + row * a.ld * TO::BYTES;
   if (a.mask && a.mask[row] == 0) {
     masked_row<TI, TO, NT>(a, row, grow, 0, a.nvec, true);
     return;
   }
-  if constexpr (!DENSE) {
-    for (int w = tid; w < kFilterWords; w += NT) c.filter[w] = 0u;
-    if (tid < 64) load_cache<TI>(a, row, zrow, c);
+  for (int w = tid; w < kFilterWords; w += NT) c.filter[w] = 0u;
+  if (a.N >= kJitterMinRows) {  // see k_row_resident
+    const uint32_t n = ((uint32_t)row * 0x9E3779B1u) >> 29;
+    for (uint32_t i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(32);
   }
-  Stats st = lane_stats<TI, DENSE, NT>(zrow, yrow, 0, a.nvec, a.nvec, a.tail);
-  st = block_merge<DENSE, NW>(st, s_red);
-  const float L = st.mz + logf(st.sz);
+  if (tid < 64) load_cache<TI>(a, row, zrow, c);
+  const uint32_t nvec = (uint32_t)a.nvec;  // > NR * NT (wide_row)
+  const bool ragged = a.tail != EPV;
+  Vec x[NR];
+#pragma unroll
+  for (uint32_t s = 0; s < NR; ++s) x[s] = ld_nt<TI>((const Vec*)zrow + s * NT, (uint32_t)tid);
 
-  if constexpr (DENSE) {
-    const DenseRow d = dense_row<EST>(st);
-    if (tid == 0) {
-      a.loss[row] = d.loss;
-      if (a.lse_out) a.lse_out[row] = d.Lz;
-    }
-    const DenseGrad dk = dense_grad_consts(d, a.gamma);
-    for (int64_t v = tid; v < a.nvec; v += NT) {
-      float g[EPV];
-      dense_grad<TI, EST>(ld_cached<TI>(zrow, v), ld_cached<TI>(yrow, v), dk, g);
-      store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
-    }
-  } else {
-    if (tid < 64) finish_row<TI, EST>(a, row, L, true, c);
-    __syncthreads();
-    const float C = c.C;
-    const bool bad = c.bad != 0;
-    const float nL = -L * kLog2e;
-    for (int64_t v = tid; v < a.nvec; v += NT) {
-      float g[EPV];
-      if constexpr (is_mc(EST)) {
-        float f[EPV];
-        unpack<TI>(ld_cached<TI>(zrow, v), f);
+  // sweep 1: the slots that are not in registers, B loads at a time
+  Stats st = stats_empty();
+  uint32_t slot = 0;  // among those
+  for (uint32_t v = NR * NT + tid; v < nvec; v += B * NT, slot += B) {
+    Vec q[B];
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) g[e] = C * fast_exp2(fmaf(f[e], kLog2e, nL));
-      } else {
+    for (int b = 0; b < B; ++b) q[b] = ld_cached<TI>(zrow, min(v + b * NT, nvec - 1));
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) g[e] = 0.f;
-      }
-      apply_spikes<EPV>(v, g, a.K, c);
-      if (bad)
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) g[e] = __builtin_nanf("");
-      store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
+    for (int b = 0; b < B; ++b) {
+      if (v + b * NT >= nvec) break;
+      if (ragged && v + b * NT == nvec - 1) mask_tail<TI>(q[b], a.tail);
+      stats_add<TI, false>(st, q[b], q[b]);
+      if constexpr (is_mc(EST))
+        if (slot + b < NL) s_z[slot + b][tid] = q[b];  // (read back by this lane only)
     }
+  }
+  // then the registers: their max, and their sum at the lane's max
+  {
+    float mx = st.mz;
+#pragma unroll
+    for (uint32_t s = 0; s < NR; ++s) {
+      float f[EPV];
+      unpack<TI>(x[s], f);
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) mx = fmaxf(mx, f[e]);
+    }
+#pragma unroll
+    for (uint32_t s = 0; s < NR; ++s) keep_packed(x[s]);
+    float sum = st.sz * rescale(st.mz, mx);
+    const float nm = mx != kNegInf ? -mx * kLog2e : 0.f;
+#pragma unroll
+    for (uint32_t s = 0; s < NR; ++s) {
+      float f[EPV];
+      unpack<TI>(x[s], f);
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) sum += fast_exp2(fmaf(f[e], kLog2e, nm));
+    }
+#pragma unroll
+    for (uint32_t s = 0; s < NR; ++s) keep_packed(x[s]);
+    st.mz = mx;
+    st.sz = sum;
+  }
+  st = block_merge_tree<false, NW>(st, s_red);
+  const float L = st.mz + logf(st.sz);
+  if (tid < 64) finish_row<TI, EST>(a, row, L, true, c);
+  __syncthreads();
+  const bool bad = c.bad != 0;
+  const float C = bad ? __builtin_nanf("") : c.C;
+  const float g0 = bad ? __builtin_nanf("") : 0.f;
+  const float nL = -L * kLog2e;
+
+  // sweep 2: what is on chip, then the rest, whose first loads go ahead of it
+  const uint32_t v0 = (NR + NL) * NT + tid;
+  auto grad_vec = [&](const Vec& z, uint32_t v) {
+    float g[EPV];
+    if constexpr (is_mc(EST)) {
+      float f[EPV];
+      unpack<TI>(z, f);
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) g[e] = C * fast_exp2(fmaf(f[e], kLog2e, nL));
+    } else {
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) g[e] = g0;
+    }
+    apply_spikes<EPV>(v, g, a.K, c);
+    store_vec<TI, TO>(grow, v, g, v == nvec - 1 ? a.tail : EPV);
+  };
+  Vec q[B];
+  if constexpr (is_mc(EST)) {
+#pragma unroll
+    for (int b = 0; b < B; ++b) q[b] = ld_cached<TI>(zrow, min(v0 + b * NT, nvec - 1));
+  }
+#pragma unroll
+  for (uint32_t s = 0; s < NR; ++s) grad_vec(x[s], s * NT + tid);
+#pragma unroll 1
+  for (uint32_t s = 0; s < NL; ++s) {
+    const uint32_t v = (NR + s) * NT + tid;
+    if (v < nvec) grad_vec(s_z[is_mc(EST) ? s : 0][tid], v);
+  }
+#pragma unroll 1
+  for (uint32_t v = v0; v < nvec; v += B * NT) {
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const Vec z = q[b];
+      if constexpr (is_mc(EST)) q[b] = ld_cached<TI>(zrow, min(v + (B + b) * NT, nvec - 1));
+      if (v + b * NT < nvec) grad_vec(z, v + b * NT);
+    }
+  }
+}
+
+// One 1024-lane workgroup per row, streaming two rows: sweep 1 reads them,
+// sweep 2 reads them again (plain loads, so the second read can hit L2 or the
+// Infinity Cache).  For the dense estimators on rows wider than
+// k_row_dense_resident holds.
+template <class TI, class TO, int EST>
+__global__ void __launch_bounds__(kRowThreads) k_row_stream(Args a) {
+  constexpr int NT = kRowThreads, NW = NT / 64, EPV = TI::EPV;
+  static_assert(is_dense(EST), "the other estimators' wide rows take k_row_wide");
+  __shared__ Stats s_red[NW];
+  const int tid = threadIdx.x;
+  const int64_t row = xcd_remap(blockIdx.x, gridDim.x);
+  const void* zrow = (const char*)a.logits + row * a.ld * TI::BYTES;
+  const void* yrow = (const char*)a.teacher + row * a.ld * TI::BYTES;
+  void* grow = (char*)a.dlogits + row * a.ld * TO::BYTES;
+  if (a.mask && a.mask[row] == 0) {
+    masked_row<TI, TO, NT>(a, row, grow, 0, a.nvec, true);
+    return;
+  }
+  Stats st = lane_stats<TI, true, NT>(zrow, yrow, 0, a.nvec, a.nvec, a.tail);
+  st = block_merge<true, NW>(st, s_red);
+  const DenseRow d = dense_row<EST>(st);
+  if (tid == 0) {
+    a.loss[row] = d.loss;
+    if (a.lse_out) a.lse_out[row] = d.Lz;
+  }
+  const DenseGrad dk = dense_grad_consts(d, a.gamma);
+  for (int64_t v = tid; v < a.nvec; v += NT) {
+    float g[EPV];
+    dense_grad<TI, EST>(ld_cached<TI>(zrow, v), ld_cached<TI>(yrow, v), dk, g);
+    store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
   }
 }
 
@@ -1234,7 +1336,7 @@ hipError_t row_t(const Args& a, Path path, bool read, hipStream_t s) {
       constexpr int NS = slots_large(TI::BYTES == 2 ? BF16 : F32);
       hipLaunchKernelGGL((k_row_resident<TI, TO, EST, NS, false>), grid, block, 0, s, a);
     } else {
-      hipLaunchKernelGGL((k_row_stream<TI, TO, EST>), grid, block, 0, s, a);
+      hipLaunchKernelGGL((k_row_wide<TI, TO, EST>), grid, block, 0, s, a);
     }
   }
   return hipGetLastError();

@@ -246,6 +246,33 @@ def test_large_support_on_the_streaming_path(est, rows):
         compare("%s/%s K=%d" % (est, rows, K), w, d, est, out, oracle_for(w, d, est, None))
 
 
+@pytest.mark.parametrize("dtype,V,ld", [
+    (synth.F32, 77828, 77832),    # one vector more than the registers of the resident kernel
+    (synth.F32, 110593, 110600),  # one element in the first slot that is read again
+    (synth.F32, 126976, 126976),  # whole slots, four of them read again
+    (synth.F32, 131075, 131080),  # a fifth, with a partial last vector
+    (synth.BF16, 155655, 155656),
+    (synth.BF16, 221185, 221192),  # one element in the first slot that is read again
+])
+@pytest.mark.parametrize("est", ["rkl_mc", "fkl_topk", "rkl_topk_trunc"])
+def test_wide_rows(est, dtype, V, ld):
+    """Rows kept partly on chip: the edges of their register, LDS and re-read
+    parts, with a masked row, both gradient types and the optional outputs."""
+    w = synth.MC16.replace(N=3, V=V, M=65, k=65, dtype=dtype, seed=V)
+    d = synth.generate(w, ld=ld)
+    mask = np.array([1, 0, 1], np.uint8)
+    say("wide %s V=%d" % (est, V))
+    ids, tau, beta = cache_arrays(d, est)
+    ref = oracle.rows(est, oracle_dtype(dtype), d["logits"], V, ids=ids, tau=tau, beta=beta,
+                      mask=mask, gamma=-0.5)
+    for out_dt in (torch.float32, torch.bfloat16):
+        out = run_gpu(to_dev(d["logits"])[:, :V], est, ids, tau, beta, mask=mask, grad_scale=-0.5,
+                      flags=opd.FLAG_FORCE_ROWWISE, want_lse=True, want_gathered=True,
+                      dlogits_dtype=out_dt)
+        compare("wide/%s/%d" % (est, V), w, d, est, out, ref, mask, gamma=-0.5,
+                bf16_out=out_dt == torch.bfloat16)
+
+
 def test_mc_duplicate_samples_accumulate():
     """Samples are iid with replacement (App. E): repeated ids are separate
     terms of the average, so their gradient spikes add."""
