@@ -73,7 +73,8 @@ __device__ __forceinline__ I xcd_remap_t(I b, I G) {
   const I q = b / kXcds;  // b's place in its XCD's dispatch order
   return (q / B) * span + (b % kXcds) * B + q % B;
 }
-__device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t G) { return xcd_remap_t(b, G); }
+// (a grid has fewer than 2^32 workgroups; 64-bit divisions are long sequences)
+__device__ __forceinline__ int64_t xcd_remap(uint32_t b, uint32_t G) { return xcd_remap_t(b, G); }
 
 // One contiguous eighth of a one-shot grid per XCD (32-bit indices).  For
 // grids of short workgroups that each write one 16 KiB piece; measured on a

@@ -418,14 +418,21 @@ __device__ __forceinline__ void finish_row(const Args& a, int64_t row, float L, 
 // times: 3.54 ms).
 constexpr int64_t kJitterMinRows = 4096;
 
-// One 1024-lane workgroup per token row, the whole row held in registers
+// One workgroup per token row (NT lanes), the whole row held in registers
 // between the sweeps (NSLOT 16-byte vectors per lane): HBM sees one read of
 // the logits and one write of the gradient.  TAIL: V is not a multiple of
 // the elements per vector, so the row's last vector is masked past V after
 // its load and stored element by element.
-template <class TI, class TO, int EST, int NSLOT, bool TAIL>
-__global__ void __launch_bounds__(kRowThreads) k_row_resident(Args a) {
-  constexpr int NT = kRowThreads, NW = NT / 64, EPV = TI::EPV;
+// Narrower rows take fewer slots, and fewer lanes: NT lanes of NSLOT slots
+// (resident_t); up to 32 registers of row data leave room for several
+// workgroups on a CU, whose loads and stores then overlap by themselves.
+constexpr bool shares_cu(int nslot, int elem_bytes) {
+  return nslot * elem_bytes * kElemsPerVec <= 32 * 4;
+}
+
+template <class TI, class TO, int EST, int NT, int NSLOT, bool TAIL>
+__global__ void __launch_bounds__(NT, shares_cu(NSLOT, TI::BYTES) ? 8 : 4) k_row_resident(Args a) {
+  constexpr int NW = NT / 64, EPV = TI::EPV;
   static_assert(!is_dense(EST), "dense estimators stream two rows");
   __shared__ float s_red[NW];
   __shared__ CacheLds c;
@@ -449,7 +456,7 @@ __global__ void __launch_bounds__(kRowThreads) k_row_resident(Args a) {
   // fall into step: they load together and store together, and HBM idles
   // between the bursts.  A wait of 0..7 x 2048 cycles, a hash of the row,
   // keeps them out of step.
-  if (a.N >= kJitterMinRows) {
+  if (!shares_cu(NSLOT, TI::BYTES) && a.N >= kJitterMinRows) {
     const uint32_t n = ((uint32_t)row * 0x9E3779B1u) >> 29;
     for (uint32_t i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(32);
   }
@@ -1293,6 +1300,41 @@ __global__ void __launch_bounds__(256) k_validate(const int32_t* ids, const floa
 
 // ---------------------------------------------------------------- dispatch
 
+// k_row_resident with the fewest slots that hold the row.  (A partial last
+// vector takes the variant that masks it and stores it element by element.)
+// Measured, 16-sample MC over 8,192 bf16 rows, us against 1,024 lanes of 38
+// slots (odd V) or of 16 and 38 (V a multiple of 4): V = 2,000 33 / 255; 6,001
+// 74 / 750; 16,384 144 / 295; 24,743 254 / 777; 65,001 617 / 912; 80,000 789 /
+// 929; 120,001 1,192 / 1,309.  Over 100 rows of 6,001: 9.2 / 21.0.
+template <class TI, class TO, int EST, int NT, int NSLOT>
+hipError_t resident_as(const Args& a, hipStream_t s) {
+  const dim3 grid((unsigned)a.N), block(NT);
+  if (a.tail != TI::EPV)
+    hipLaunchKernelGGL((k_row_resident<TI, TO, EST, NT, NSLOT, true>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_row_resident<TI, TO, EST, NT, NSLOT, false>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+template <class TI, class TO, int EST>
+hipError_t resident_t(const Args& a, hipStream_t s) {
+  constexpr int DT = TI::BYTES == 2 ? BF16 : F32, NS = slots_small(DT);
+  const int64_t n = a.nvec;
+  if constexpr (is_mc(EST)) {
+    if (n <= 4 * 256) return resident_as<TI, TO, EST, 256, 4>(a, s);
+    if (n <= NS * 256) return resident_as<TI, TO, EST, 256, NS>(a, s);
+    if (n <= NS * 512) return resident_as<TI, TO, EST, 512, NS>(a, s);
+    if (n <= NS * 1024) return resident_as<TI, TO, EST, 1024, NS>(a, s);
+    // one workgroup to a CU from here: three steps up to the widest
+    if (n <= NS * 3 / 2 * 1024) return resident_as<TI, TO, EST, 1024, NS * 3 / 2>(a, s);
+    if (n <= (NS * 2 - 1) * 1024) return resident_as<TI, TO, EST, 1024, NS * 2 - 1>(a, s);
+  } else {
+    // (the restricted KLs write zeros, so their statistics alone are at stake)
+    if (n <= NS * 256) return resident_as<TI, TO, EST, 256, NS>(a, s);
+    if (n <= NS * 1024) return resident_as<TI, TO, EST, 1024, NS>(a, s);
+  }
+  return resident_as<TI, TO, EST, 1024, slots_large(DT)>(a, s);
+}
+
 template <class TI, class TO, int EST>
 hipError_t row_t(const Args& a, Path path, bool read, hipStream_t s) {
   const dim3 grid((unsigned)a.N), block(kRowThreads);
@@ -1324,17 +1366,8 @@ hipError_t row_t(const Args& a, Path path, bool read, hipStream_t s) {
   } else {
     if (!read) {
       return hipErrorInvalidValue;  // the write-only top-k form runs launch_topk_sparse
-    } else if (a.tail != TI::EPV && path != Path::RowStream) {
-      // a partial last vector: the variant that masks and stores it element
-      // by element (the others keep whole-vector code)
-      constexpr int NS = slots_large(TI::BYTES == 2 ? BF16 : F32);
-      hipLaunchKernelGGL((k_row_resident<TI, TO, EST, NS, true>), grid, block, 0, s, a);
-    } else if (path == Path::RowResidentSmall) {
-      constexpr int NS = slots_small(TI::BYTES == 2 ? BF16 : F32);
-      hipLaunchKernelGGL((k_row_resident<TI, TO, EST, NS, false>), grid, block, 0, s, a);
-    } else if (path == Path::RowResidentLarge) {
-      constexpr int NS = slots_large(TI::BYTES == 2 ? BF16 : F32);
-      hipLaunchKernelGGL((k_row_resident<TI, TO, EST, NS, false>), grid, block, 0, s, a);
+    } else if (path != Path::RowStream) {
+      return resident_t<TI, TO, EST>(a, s);
     } else {
       hipLaunchKernelGGL((k_row_wide<TI, TO, EST>), grid, block, 0, s, a);
     }

@@ -273,6 +273,28 @@ def test_wide_rows(est, dtype, V, ld):
                 bf16_out=out_dt == torch.bfloat16)
 
 
+@pytest.mark.parametrize("dtype,V", [
+    (dt, V + d)
+    for dt, widths in ((synth.BF16, (4096, 16384, 32768, 65536, 98304, 126976, 155648)),
+                       (synth.F32, (4096, 8192, 16384, 32768, 49152, 61440, 77824)))
+    for V in widths for d in (-1, 0, 1) if V + d not in (155649, 77825)])
+@pytest.mark.parametrize("est", ["rkl_mc", "rkl_topk"])
+def test_resident_row_classes(est, dtype, V):
+    """The widest row of each size class of the register-resident kernel, one
+    entry less (a partial last vector) and one more (the next class)."""
+    ld = (V + 7) // 8 * 8
+    w = synth.MC16.replace(N=3, V=V, M=5, k=5, dtype=dtype, seed=V)
+    d = synth.generate(w, ld=ld)
+    mask = np.array([1, 0, 1], np.uint8)
+    say("class %s V=%d" % (est, V))
+    ids, tau, beta = cache_arrays(d, est)
+    ref = oracle.rows(est, oracle_dtype(dtype), d["logits"], V, ids=ids, tau=tau, beta=beta,
+                      mask=mask, gamma=0.5)
+    out = run_gpu(to_dev(d["logits"])[:, :V], est, ids, tau, beta, mask=mask, grad_scale=0.5,
+                  flags=opd.FLAG_FORCE_ROWWISE, want_lse=True, want_gathered=True)
+    compare("class/%s/%d" % (est, V), w, d, est, out, ref, mask, gamma=0.5)
+
+
 def test_mc_duplicate_samples_accumulate():
     """Samples are iid with replacement (App. E): repeated ids are separate
     terms of the average, so their gradient spikes add."""
