@@ -17,11 +17,19 @@ using opd::Path;
 // rows over more workgroups outweighs the split path's second read of each
 // row.  Measured on MI355X (16-sample MC, V = 151,936 bf16, inputs rotated
 // so no step finds the last one's rows in the Infinity Cache), mean time per
-// call, split against row path: N = 16: 24.8 against 30.5 us; 24: 23.5
-// against 29.7; 32: 24.6 against 31.0; 48: 28.3 against 29.6; 64: 32.5
-// against 31.0; 128: 54.8 against 37.2.
+// call, split against row path: N = 8: 10.2 against 22.7 us; 24: 13.6 against
+// 23.3; 48: 17.9 against 23.6; 63: 19.6 against 23.9; more rows 128: 44.9
+// against 31.3.  Dense: N = 63: 25.2 against 30.5.
 constexpr int64_t kSplitMaxRows = 64;
-// Workgroups the split path aims for, and its largest chunk count.
+// Workgroups the split path aims for below kSplitMaxRows: six to a CU, all of
+// them resident at once (two or three rounds of shorter ones repeat the rows'
+// merge and estimator in each).  Against 8,192 (64 chunks per row, as before),
+// V = 151,936: bf16 MC N = 48: 17.9 against 21.2 us; 63: 19.6 against 24.6;
+// fp32 63: 24.1 / 30.9; dense bf16 63: 25.2 / 31.4; V = 60,000 48: 13.1 / 18.7.
+// 512 and 1,024: 23.4 and 22.2 us where 1,536 takes 19.6.
+constexpr int64_t kSplitResidentGroups = 1536;
+// The workspace's size, and the chunks of forced calls over more rows, come
+// from this target and the largest chunk count.
 constexpr int64_t kSplitTargetGroups = 8192;
 constexpr int kSplitMaxChunks = 64;
 
@@ -90,7 +98,9 @@ struct Plan {
 };
 
 // The split-path layout for N rows of nvec vectors: enough chunks for about
-// kSplitTargetGroups workgroups, each chunk at least one vector per lane.
+// kSplitTargetGroups workgroups (kSplitResidentGroups below kSplitMaxRows
+// rows), each chunk at least one vector per lane.  The workspace is sized for
+// the former, so a size that serves some rows serves fewer.
 Plan split_plan(int64_t N, int64_t nvec) {
   Plan p{true, 1, nvec, 0};
   int64_t P = (kSplitTargetGroups + N - 1) / N;
@@ -98,9 +108,11 @@ Plan split_plan(int64_t N, int64_t nvec) {
   if (P > by_width) P = by_width;
   if (P > kSplitMaxChunks) P = kSplitMaxChunks;
   if (P < 1) P = 1;
+  p.ws_bytes = (size_t)N * (size_t)P * opd::kPartialFloats * sizeof(float);
+  const int64_t resident = (kSplitResidentGroups + N - 1) / N;
+  if (N < kSplitMaxRows && P > resident) P = resident;
   p.P = (int)P;
   p.chunk_vec = (nvec + P - 1) / P;
-  p.ws_bytes = (size_t)N * (size_t)P * opd::kPartialFloats * sizeof(float);
   return p;
 }
 
@@ -330,8 +342,17 @@ int loss_call(const void* logits, int32_t dtype, int64_t N, int64_t V, int64_t l
   const int epv = elems_per_vec(dtype);
   const int tail = (int)(V - (nvec - 1) * epv);
 
+  // Rows of the register-resident kernel's classes that share a CU take it
+  // whatever N is: one launch of one read.  Measured, split against row path,
+  // 16-sample MC: V = 20,000 bf16 N = 8: 9.2 against 8.8 us; 63: 11.9 / 9.4; V
+  // = 32,000 N = 24: 11.3 / 9.6; 63: 15.0 / 10.0.  Wider ones are split: V =
+  // 60,000 N = 8: 9.5 / 11.7.  (Dense rows have no such class: V = 32,000 N =
+  // 63: 13.0 / 16.3.)
+  const bool narrow = !est_dense(estimator) && !(o.flags & OPD_FLAG_FORCE_SPLITV) &&
+                      nvec <= (int64_t)opd::slots_small(dtype) * (opd::kRowThreads / 2);
+
   Plan plan{false, 1, nvec, 0};
-  if (split_wanted(N, o.flags)) {
+  if (split_wanted(N, o.flags) && !narrow) {
     const Plan sp = split_plan(N, nvec);
     if (scratch) {
       // the no-allocation entry point: the library's static scratch array,

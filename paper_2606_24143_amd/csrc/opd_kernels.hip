@@ -823,36 +823,32 @@ __global__ void __launch_bounds__(kRowThreads) k_row_dense_resident(Args a) {
     sweep2(std::false_type{});
 }
 
-// Sweep-1 statistics of vectors [v0, v1) of a row, one lane's share
-// (stride NT), with two loads in flight per step.
-template <class TI, bool DENSE, int NT>
+// Sweep-1 statistics of vectors [v0, v1) of a row (v0 < v1), one lane's share
+// (stride NT), with B loads of each row in flight per step.
+template <class TI, bool DENSE, int NT, int B>
 __device__ __forceinline__ Stats lane_stats(const void* zrow, const void* yrow, int64_t v0,
                                             int64_t v1, int64_t nvec, int tail) {
   constexpr int EPV = TI::EPV;
   Stats s = stats_empty();
-  int64_t v = v0 + threadIdx.x;
-  for (; v + NT < v1; v += 2 * NT) {
-    typename TI::Vec z0 = ld_cached<TI>(zrow, v), z1 = ld_cached<TI>(zrow, v + NT);
-    typename TI::Vec y0 = z0, y1 = z1;
-    if constexpr (DENSE) {
-      y0 = ld_cached<TI>(yrow, v);
-      y1 = ld_cached<TI>(yrow, v + NT);
+  for (int64_t v = v0 + threadIdx.x; v < v1; v += B * NT) {
+    typename TI::Vec z[B], y[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      if (v - threadIdx.x + b * NT >= v1) break;  // (wave-uniform)
+      const int64_t vb = v + b * NT < v1 ? v + b * NT : v1 - 1;
+      z[b] = ld_cached<TI>(zrow, vb);
+      if constexpr (DENSE) y[b] = ld_cached<TI>(yrow, vb);
     }
-    if (tail != EPV && v + NT == nvec - 1) {
-      mask_tail<TI>(z1, tail);
-      if constexpr (DENSE) mask_tail<TI>(y1, tail);
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      if (v + b * NT >= v1) break;
+      if constexpr (!DENSE) y[b] = z[b];
+      if (tail != EPV && v + b * NT == nvec - 1) {
+        mask_tail<TI>(z[b], tail);
+        if constexpr (DENSE) mask_tail<TI>(y[b], tail);
+      }
+      stats_add<TI, DENSE>(s, z[b], y[b]);
     }
-    stats_add<TI, DENSE>(s, z0, y0);
-    stats_add<TI, DENSE>(s, z1, y1);
-  }
-  if (v < v1) {
-    typename TI::Vec z0 = ld_cached<TI>(zrow, v), y0 = z0;
-    if constexpr (DENSE) y0 = ld_cached<TI>(yrow, v);
-    if (tail != EPV && v == nvec - 1) {
-      mask_tail<TI>(z0, tail);
-      if constexpr (DENSE) mask_tail<TI>(y0, tail);
-    }
-    stats_add<TI, DENSE>(s, z0, y0);
   }
   return s;
 }
@@ -1009,7 +1005,7 @@ __global__ void __launch_bounds__(kRowThreads) k_row_stream(Args a) {
     masked_row<TI, TO, NT>(a, row, grow, 0, a.nvec, true);
     return;
   }
-  Stats st = lane_stats<TI, true, NT>(zrow, yrow, 0, a.nvec, a.nvec, a.tail);
+  Stats st = lane_stats<TI, true, NT, 2>(zrow, yrow, 0, a.nvec, a.nvec, a.tail);
   st = block_merge<true, NW>(st, s_red);
   const DenseRow d = dense_row<EST>(st);
   if (tid == 0) {
@@ -1030,6 +1026,14 @@ __global__ void __launch_bounds__(kRowThreads) k_row_stream(Args a) {
 // merges the P records of its row in a fixed order (the same in every chunk
 // of the row, so every chunk sees bit-identical row constants), repeats the
 // K-entry estimator, and writes its chunk of the gradient.
+// Both passes are bound by latency, so a lane requests kSplitAhead vectors at
+// once, in pass 2 before the row's constants are known, beside the chain of
+// cache entries, gathered logits and merge that they come from.  Measured, 16-
+// sample MC, V = 151,936, one at a time in pass 2 and two in pass 1 against
+// four: bf16 24 rows 14.6 against 13.6 us, 63 rows 25.0 / 19.6, fp32 30.4 /
+// 24.1 (with the chunks of split_plan).  Eight hold fewer workgroups on a CU:
+// fp32 24 rows 17.9.
+constexpr int kSplitAhead = 4;
 
 template <class TI, bool DENSE>
 __global__ void __launch_bounds__(kSplitThreads) k_split_stats(Args a) {
@@ -1043,7 +1047,7 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_stats(Args a) {
   const int64_t v1 = v0 + a.chunk_vec < a.nvec ? v0 + a.chunk_vec : a.nvec;
   const void* zrow = (const char*)a.logits + row * a.ld * TI::BYTES;
   const void* yrow = DENSE ? (const char*)a.teacher + row * a.ld * TI::BYTES : nullptr;
-  Stats st = lane_stats<TI, DENSE, NT>(zrow, yrow, v0, v1, a.nvec, a.tail);
+  Stats st = lane_stats<TI, DENSE, NT, kSplitAhead>(zrow, yrow, v0, v1, a.nvec, a.tail);
   st = block_merge<DENSE, NW>(st, s_red);
   if (threadIdx.x == 0) {
     float* p = a.ws + ((size_t)row * a.P + chunk) * kPartialFloats;
@@ -1054,7 +1058,7 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_stats(Args a) {
 
 template <class TI, class TO, int EST>
 __global__ void __launch_bounds__(kSplitThreads) k_split_write(Args a) {
-  constexpr int NT = kSplitThreads, EPV = TI::EPV;
+  constexpr int NT = kSplitThreads, EPV = TI::EPV, B = kSplitAhead;
   constexpr bool DENSE = is_dense(EST);
   __shared__ CacheLds c;
   __shared__ Stats s_row;
@@ -1074,19 +1078,47 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_write(Args a) {
   if constexpr (!DENSE) {
     for (int w = tid; w < kFilterWords; w += NT) c.filter[w] = 0u;
   }
+  Stats s = stats_empty();
   if (tid < 64) {
-    if constexpr (!DENSE) load_cache<TI>(a, row, zrow, c);
-    Stats s = stats_empty();
     if (tid < a.P) {
       const float* p = a.ws + ((size_t)row * a.P + tid) * kPartialFloats;
       s = Stats{p[0], p[1], p[2], p[3], p[4], p[5]};
     }
+    if constexpr (!DENSE) load_cache<TI>(a, row, zrow, c);
+  }
+  typename TI::Vec z[B], y[B];
+  auto fetch = [&](int b, int64_t vb) {  // the lane's vector of those from vb on
+    if (vb >= v1) return;
+    const int64_t v = vb + tid < v1 ? vb + tid : v1 - 1;
+    if constexpr (DENSE || is_mc(EST)) z[b] = ld_cached<TI>(zrow, v);
+    if constexpr (DENSE) y[b] = ld_cached<TI>(yrow, v);
+  };
+#pragma unroll
+  for (int b = 0; b < B; ++b) fetch(b, v0 + b * NT);
+  if (tid < 64) {
     s = wave_merge<DENSE>(s);
     if (tid == 0) s_row = s;
   }
   __syncthreads();
   const Stats st = s_row;
   const float L = st.mz + logf(st.sz);
+  // the chunk's gradient, grad(z, y, v, g) giving that of vector v
+  auto write = [&](auto grad) {
+    for (int64_t vb = v0; vb < v1; vb += B * NT) {
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        const int64_t v = vb + b * NT + tid;
+        typename TI::Vec zv{}, yv{};
+        if constexpr (DENSE || is_mc(EST)) zv = z[b];
+        if constexpr (DENSE) yv = y[b];
+        fetch(b, vb + (B + b) * NT);
+        if (v >= v1) continue;
+        float g[EPV];
+        grad(zv, yv, v, g);
+        store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
+      }
+    }
+  };
   if constexpr (DENSE) {
     const DenseRow d = dense_row<EST>(st);
     if (chunk == 0 && tid == 0) {
@@ -1094,22 +1126,17 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_write(Args a) {
       if (a.lse_out) a.lse_out[row] = d.Lz;
     }
     const DenseGrad dk = dense_grad_consts(d, a.gamma);
-    for (int64_t v = v0 + tid; v < v1; v += NT) {
-      float g[EPV];
-      dense_grad<TI, EST>(ld_cached<TI>(zrow, v), ld_cached<TI>(yrow, v), dk, g);
-      store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
-    }
+    write([&](auto zv, auto yv, int64_t, float (&g)[EPV]) { dense_grad<TI, EST>(zv, yv, dk, g); });
   } else {
     if (tid < 64) finish_row<TI, EST>(a, row, L, chunk == 0, c);
     __syncthreads();
     const float C = c.C;
     const bool bad = c.bad != 0;
     const float nL = -L * kLog2e;
-    for (int64_t v = v0 + tid; v < v1; v += NT) {
-      float g[EPV];
+    write([&](auto zv, auto, int64_t v, float (&g)[EPV]) {
       if constexpr (is_mc(EST)) {
         float f[EPV];
-        unpack<TI>(ld_cached<TI>(zrow, v), f);
+        unpack<TI>(zv, f);
 #pragma unroll
         for (int e = 0; e < EPV; ++e) g[e] = C * fast_exp2(fmaf(f[e], kLog2e, nL));
       } else {
@@ -1120,8 +1147,7 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_write(Args a) {
       if (bad)
 #pragma unroll
         for (int e = 0; e < EPV; ++e) g[e] = __builtin_nanf("");
-      store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
-    }
+    });
   }
 }
 

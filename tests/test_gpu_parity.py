@@ -295,6 +295,50 @@ def test_resident_row_classes(est, dtype, V):
     compare("class/%s/%d" % (est, V), w, d, est, out, ref, mask, gamma=0.5)
 
 
+@pytest.mark.parametrize("dtype,V", [
+    (synth.BF16, 65540),   # 256 vectors to a chunk, the last one short
+    (synth.BF16, 262144),  # 1,024: one step of the four vectors a lane requests
+    (synth.F32, 262145),   # one vector in the second step, which the last lacks
+    (synth.BF16, 530001),  # a third step and a partial last vector
+])
+@pytest.mark.parametrize("est", ["rkl_mc", "fkl_topk", "rkl_dense"])
+def test_split_chunk_edges(est, dtype, V):
+    """Chunks of the split path whose lanes hold one to three steps of vectors."""
+    ld = (V + 7) // 8 * 8
+    w = synth.Workload("t_split", N=3, V=V, dtype=dtype, estimators=ALL, k=16, M=6,
+                       sigma_student=2.5, sigma_teacher=1.0, sigma_behaviour=0.5,
+                       dense_teacher=True, seed=V)
+    d = synth.generate(w, ld=ld)
+    mask = np.array([1, 0, 1], np.uint8)
+    say("split %s V=%d" % (est, V))
+    teacher = to_dev(d["teacher_logits"])[:, :V] if est in DENSE else None
+    ids, tau, beta = cache_arrays(d, est)
+    out = run_gpu(to_dev(d["logits"])[:, :V], est, ids, tau, beta, teacher, mask=mask,
+                  grad_scale=0.75, flags=opd.FLAG_FORCE_SPLITV, want_lse=True,
+                  want_gathered=est not in DENSE)
+    ref = oracle_for(w, d, est, mask, gamma=0.75)
+    compare("split/%s/%d" % (est, V), w, d, est, out, ref, mask, gamma=0.75)
+
+
+@pytest.mark.parametrize("N,V", [(1, 32768), (63, 32768), (1, 32776), (24, 32772), (63, 32772),
+                                 (63, 151933)])
+def test_few_rows_choose_their_path(N, V):
+    """The widest row that stays whole below 64 rows, and split ones at the
+    row counts where the chunks change."""
+    ld = (V + 7) // 8 * 8
+    w = synth.MC16.replace(N=N, V=V, M=16, seed=N + V)
+    d = synth.generate(w, ld=ld)
+    mask = np.ones(N, np.uint8)
+    mask[1::5] = 0
+    say("few rows N=%d V=%d" % (N, V))
+    ids, tau, beta = cache_arrays(d, "rkl_mc")
+    out = run_gpu(to_dev(d["logits"])[:, :V], "rkl_mc", ids, tau, beta, mask=mask,
+                  grad_scale=0.5, want_lse=True, want_gathered=True)
+    ref = oracle.rows("rkl_mc", oracle_dtype(w.dtype), d["logits"], V, ids=ids, tau=tau, beta=beta,
+                      mask=mask, gamma=0.5)
+    compare("few/%d/%d" % (N, V), w, d, "rkl_mc", out, ref, mask, gamma=0.5)
+
+
 def test_mc_duplicate_samples_accumulate():
     """Samples are iid with replacement (App. E): repeated ids are separate
     terms of the average, so their gradient spikes add."""
