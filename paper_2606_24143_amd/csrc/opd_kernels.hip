@@ -1028,11 +1028,11 @@ __global__ void __launch_bounds__(kRowThreads) k_row_stream(Args a) {
 // K-entry estimator, and writes its chunk of the gradient.
 // Both passes are bound by latency, so a lane requests kSplitAhead vectors at
 // once, in pass 2 before the row's constants are known, beside the chain of
-// cache entries, gathered logits and merge that they come from.  Measured, 16-
-// sample MC, V = 151,936, one at a time in pass 2 and two in pass 1 against
-// four: bf16 24 rows 14.6 against 13.6 us, 63 rows 25.0 / 19.6, fp32 30.4 /
-// 24.1 (with the chunks of split_plan).  Eight hold fewer workgroups on a CU:
-// fp32 24 rows 17.9.
+// cache entries, gathered logits and merge that they come from.  Measured with
+// two, four and eight at V = 151,936 and the chunks of split_plan: 16-sample MC
+// fp32, 63 rows 25.4, 24.1 and 27.4 us; dense bf16, 63 rows 26.7, 25.2 and 26.6
+// (eight hold fewer workgroups on a CU).  At 24 rows, of two or three vectors
+// per lane, it makes no difference: 13.0 us with one at a time as well.
 constexpr int kSplitAhead = 4;
 
 template <class TI, bool DENSE>
