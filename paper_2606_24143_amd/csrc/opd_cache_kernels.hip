@@ -764,10 +764,10 @@ __global__ void __launch_bounds__(kSmpThreads) k_sample(CacheArgs a) {
 // max), need no maximum.  The entries are within about 3.4e-16 relative
 // (exp_reduced: 1.5e-15).  A tile that holds any other value is summed by
 // term_any: magnitudes below 2^-17 by exp's series, logits below -820 (-inf
-// among them) as 0.  A row with a NaN, a logit of 64 or more or one in [-820,
-// -64), or whose sum is below exp(-60), is marked for k_sample_redo.  In the
-// rows that stay every term that is not 0 is at least exp(-64), and the row's
-// maximum is above -72 (its sum is at most V exp(max)), so a logit below -820
+// among them) as 0.  A row with any other value (a NaN, 64 or more, [-820,
+// -64]), or whose sum is below exp(-60), is marked for k_sample_redo.  In the
+// rows that stay every term that is not 0 is above exp(-64), and the row's
+// maximum is above -74 (its sum is at most V exp(max)), so a logit below -820
 // is 0 in double's exp(z - max) as well.
 //
 // One 1,024-lane workgroup per CU stays for all its rows, so the table is set
@@ -794,7 +794,6 @@ constexpr uint32_t kTabBase = kTabLoExp << 7;   // bf16 magnitude bits of 2^-17
 constexpr uint32_t kTabSize = (kTabHiExp - kTabLoExp) * 256;
 static_assert(kTabSize * 8 <= 65536, "a table offset in bytes has 16 bits");
 constexpr float kTabTiny = 7.62939453125e-06f;  // 2^-17
-constexpr float kTabHuge = 64.f;
 constexpr float kTabZero = -820.f;
 constexpr double kTabMinSum = 8.75651076269652e-27;  // exp(-60)
 // ids_out[row * M] of a row left to k_sample_redo
@@ -856,14 +855,18 @@ __device__ __forceinline__ u16x2 tab_index(uint32_t x) {
   return __builtin_bit_cast(u16x2, t);
 }
 
-// exp(z) of any logit of a row that stays.
-__device__ __forceinline__ double term_any(float z, const double* e) {
+// exp(z) of any logit of a row that stays; `known` is cleared by a value that
+// no such row holds.  (By what the table holds, not by bounds of its own: a
+// value is in the table, below it, 0 in double, or unknown.)
+__device__ __forceinline__ double term_any(float z, const double* e, bool& known) {
   const uint32_t b = __float_as_uint(z) >> 16;
   const uint32_t t = (((b << 1) | (b >> 15)) - 2 * kTabBase) & 0xFFFFu;
   if (t < kTabSize) return e[t];
   const double d = (double)z;
   // the next term of the series, z^4 / 24, is below 1.5e-22
-  return fabsf(z) < kTabTiny ? fma(d, fma(d, fma(d, 1.0 / 6.0, 0.5), 1.0), 1.0) : 0.0;
+  if (fabsf(z) < kTabTiny) return fma(d, fma(d, fma(d, 1.0 / 6.0, 0.5), 1.0), 1.0);
+  known = known && z < kTabZero;
+  return 0.0;
 }
 
 struct TabTerms {
@@ -873,7 +876,8 @@ struct TabTerms {
   };
   __device__ __forceinline__ Chunk chunk(int64_t) const { return Chunk{1.0}; }
   __device__ __forceinline__ double operator()(float z, const Chunk&) const {
-    return term_any(z, e);
+    bool known = true;
+    return term_any(z, e, known);
   }
 };
 
@@ -1100,7 +1104,7 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
       } else {
         // (from memory again: an index into x would put x there)
         const char* zrow = row_ptr(row_of(j));
-        bool general = false;
+        bool known = true;
 #pragma unroll 1
         for (int b = 0; b < R; ++b) {
           const uint32_t v = t0 + rowk * kSmpStepVecs + rl + 16u * b;
@@ -1108,12 +1112,9 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
           float f[4];
           unpack<TI>(load_vec<TI>(zrow, v, nvec, a.tail), f);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            general |= !(f[e] < kTabHuge) || (f[e] < -kTabHuge && f[e] >= kTabZero);
-            s0 += term_any(f[e], sh.e);
-          }
+          for (int e = 0; e < 4; ++e) s0 += term_any(f[e], sh.e, known);
         }
-        if (__ballot(general) != 0) lds_post(&sh.general[slot], j + 1);
+        if (__ballot(!known) != 0) lds_post(&sh.general[slot], j + 1);
       }
       const double sum = row16_sum(s0 + s1);
       // the slot's last row has been drawn from (see `draws`)

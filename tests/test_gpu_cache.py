@@ -267,6 +267,35 @@ def test_sample_table_rows(V, ld, N, M):
     assert np.all(np.abs(lse - ref["lse"])[defined] <= LP_TOL * (1 + np.abs(ref["lse"][defined])))
 
 
+@pytest.mark.parametrize("edge", [-64.0, -63.75, -64.5])
+def test_sample_logits_at_the_tables_lower_edge(edge):
+    """Logits at and beside -64, the lower edge of the table kernel's values,
+    in rows where they matter: as nearly all of the row's mass below a maximum
+    of -59, as all of it, and as the first entry at a uniform of 0 (the first
+    entry of positive probability)."""
+    V, N, M = 16384, 4, 16
+    x = np.full((N, V), edge, np.float32)
+    x[0, 777] = -59.0
+    rng = np.random.default_rng(6)
+    x[2] = rng.normal(0.0, 3.0, V)
+    x[2, 0] = edge
+    x[3] = -1000.0
+    x[3, 5::7] = edge
+    x[3, 9001] = -57.0
+    stored = to_stored(x, synth.BF16)
+    say("sample edge %g" % edge)
+    u = f32_uniforms(77, N, M)
+    u[:, 0] = 0.0
+    u[:, 1] = np.nextafter(np.float32(1), np.float32(0))
+    out = opd.sample_actions(as_device(stored, V), to_dev(u), want_lse=True)
+    torch.cuda.synchronize()
+    ref = oracle.cache_rows("sample", synth.BF16, stored, V, M, uniforms=u)
+    lse = out["lse"].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(lse - ref["lse"]) <= LP_TOL * (1 + np.abs(ref["lse"])))
+    check_draws("edge", out["ids"].cpu().numpy(), out["logp"].cpu().numpy(), stored, V,
+                synth.BF16, u, ref)
+
+
 @pytest.mark.slow
 def test_sample_full_size_mc16():
     w = synth.MC16
