@@ -1081,6 +1081,7 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
     if (have) {
       const uint32_t j = tj, k = tk, t0 = k * TILE, slot = j % slots;
       double s0 = 0.0, s1 = 0.0;
+      bool known = true;
       if (t0 + TILE <= nclean &&
           __ballot(top[0] >= kTabSize || top[1] >= kTabSize) == 0) {  // wave-uniform
         // (eight reads in flight: the scheduling barriers keep each batch whole)
@@ -1104,7 +1105,6 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
       } else {
         // (from memory again: an index into x would put x there)
         const char* zrow = row_ptr(row_of(j));
-        bool known = true;
 #pragma unroll 1
         for (int b = 0; b < R; ++b) {
           const uint32_t v = t0 + rowk * kSmpStepVecs + rl + 16u * b;
@@ -1114,11 +1114,12 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) s0 += term_any(f[e], sh.e, known);
         }
-        if (__ballot(!known) != 0) lds_post(&sh.general[slot], j + 1);
       }
       const double sum = row16_sum(s0 + s1);
-      // the slot's last row has been drawn from (see `draws`)
+      // the slot's last row has been drawn from (see `draws`); until then its
+      // mark and its records are still read
       lds_wait(&sh.drawn[slot], j / slots * ndraw);
+      if (__ballot(!known) != 0) lds_post(&sh.general[slot], j + 1);
       const uint32_t q = k * 4 + rowk;
       if (rl == 15 && q < nchunk) sh.s[slot * nchunk + q] = sum;
       lds_release();

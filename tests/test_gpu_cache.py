@@ -296,6 +296,56 @@ def test_sample_logits_at_the_tables_lower_edge(edge):
                 synth.BF16, u, ref)
 
 
+@pytest.mark.parametrize("V,N,M,check", [
+    (655360, 256 * 3 + 7, 16, 97),   # two slots: each is used again by the row after next
+    (16390, 256 * 10 + 3, 9, None),  # eight slots, and a short last tile
+])
+def test_sample_table_slots_are_used_again_by_marked_rows(V, N, M, check):
+    """Batches in which (nearly) every row is left to the general kernel, long
+    enough that every workgroup of the table kernel uses each slot of its ring
+    several times: a row's mark is still read by its draws while tiles of the
+    row that takes its slot are summed.  The value that marks a row is in its
+    first or its last tile; masked rows and ordinary ones lie among them."""
+    say("sample marked rows V=%d N=%d" % (V, N))
+    ld = (V + 7) // 8 * 8
+    rng = np.random.default_rng(V)
+    kinds = 8
+    base = rng.normal(0.0, 3.0, (kinds, V)).astype(np.float32)
+    for i, (at, z) in enumerate([(3, 400.0), (V - 1, -500.0), (V - 2, np.inf), (5, np.nan),
+                                 (V - 1, 400.0), (7, -500.0), (V - 3, np.nan)]):
+        base[i, at] = z
+    base[0, V // 2] = 399.0
+    kind = np.where(np.arange(N) // 256 % 5 == 4, 7, rng.integers(0, 7, N))
+    rows = np.zeros((kinds, ld), np.uint16)
+    rows[:, :V] = to_stored(base, synth.BF16)
+    stored = to_dev(rows)[to_dev(kind)]  # [N, ld] on the device
+    u = f32_uniforms(V + M, N, M)
+    u[:, 0] = 0.0
+    mask = (rng.random(N) < 0.9).astype(np.uint8)
+    # what an id that nothing writes is likely to be: the next buffer of this
+    # size is the one freed here
+    stale = torch.full((N, M), -7, dtype=torch.int32, device=DEV)
+    del stale
+    out = opd.sample_actions(stored[:, :V], to_dev(u), mask=to_dev(mask), want_lse=True)
+    torch.cuda.synchronize()
+    ids, logp, lse = (out[k].cpu().numpy() for k in ("ids", "logp", "lse"))
+    keep = mask == 1
+    undefined = np.isin(kind, (2, 3, 6))
+    assert np.all(ids[~keep] == 0) and np.all(logp[~keep] == 0) and np.all(lse[~keep] == 0)
+    assert np.all(ids[keep & undefined] == -1) and np.all(np.isnan(logp[keep & undefined]))
+    live = np.flatnonzero(keep & ~undefined)
+    assert np.all(ids[live] >= 0) and np.all(ids[live] < V)
+    # log-partitions of every row, draws of a sample of them
+    one = oracle.cache_rows("sample", synth.BF16, rows, V, 1,
+                            uniforms=np.full((kinds, 1), 0.5, np.float32))
+    want = one["lse"][kind[live]]
+    assert np.all(np.abs(lse[live] - want) <= LP_TOL * (1 + np.abs(want)))
+    pick = live if check is None else live[np.linspace(0, len(live) - 1, check).astype(int)]
+    some = rows[kind[pick]]
+    ref = oracle.cache_rows("sample", synth.BF16, some, V, M, uniforms=u[pick])
+    check_draws("marked", ids[pick], logp[pick], some, V, synth.BF16, u[pick], ref)
+
+
 @pytest.mark.slow
 def test_sample_full_size_mc16():
     w = synth.MC16
