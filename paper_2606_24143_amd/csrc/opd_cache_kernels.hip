@@ -1610,6 +1610,7 @@ __global__ void __launch_bounds__(kTkThreads) k_topk_stream(CacheArgs a) {
   bool first = true;    // this wave's first tile
   uint32_t cnt = 0;     // this lane's candidates so far
   float m = kNegInf, sum = 0.f, chk = 0.f;
+  uint32_t bare = 0;    // this lane's first tiles that hold -inf and NaN only
 
   // One tile of B vectors per lane at vector t0 (lane l holds t0 + 64 b + l).
   // Pass A, for every lane: the tile's maximum (and its share of the
@@ -1666,6 +1667,8 @@ __global__ void __launch_bounds__(kTkThreads) k_topk_stream(CacheArgs a) {
           for (int i = 0; i < h; ++i) ex[i] += ex[i + h];
         sum = fmaf(sum, rescale(m, mn), ex[0]);  // NaN from a NaN element
         m = mn;
+      } else {
+        ++bare;
       }
     }
     run = fmaxf(run, tmx);
@@ -1782,6 +1785,20 @@ __global__ void __launch_bounds__(kTkThreads) k_topk_stream(CacheArgs a) {
     for (int b = 0; b < B; ++b) xa[b] = ld_nt<TI>(zrow, min(t0 + 64u * b + lane, nvec - 1));
     process(xa, t0, Partial());
   }
+  // the tiles that were not summed, for NaN (usually none; read again here,
+  // which keeps the test out of the loop's registers)
+  if constexpr (LSE) {
+    const uint32_t v0 = (uint32_t)w * TILE + lane;
+    for (uint32_t i = 0; i < bare; ++i)
+#pragma unroll 1
+      for (uint32_t v = v0 + i * STRIDE; v < min(v0 + i * STRIDE + TILE, nvec); v += 64) {
+        float f[4];
+        unpack<TI>(load_vec<TI>(zrow, v, nvec, a.tail), f);
+        sum += (f[0] == f[0] && f[1] == f[1] && f[2] == f[2] && f[3] == f[3])
+                   ? 0.f
+                   : __builtin_nanf("");
+      }
+  }
   bool nan_seen;
   if constexpr (LSE) nan_seen = sum != sum || m == kNegInf;
   else nan_seen = chk != chk;
@@ -1885,17 +1902,16 @@ __global__ void __launch_bounds__(kScoreThreads) k_score(CacheArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) bm = fmaxf(bm, f[b][e]);
     }
+    // (as stats_add: a block of NaN has no maximum either, and is summed)
     const float mn = fmaxf(m, bm);
-    if (mn != kNegInf) {
-      float acc = sum * rescale(m, mn);
-      const float nm = -mn * kLog2e;
+    float acc = sum * rescale(m, mn);
+    const float nm = mn != kNegInf ? -mn * kLog2e : 0.f;
 #pragma unroll
-      for (int b = 0; b < B; ++b)
+    for (int b = 0; b < B; ++b)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc += ez(f[b][e], nm);
-      sum = acc;
-      m = mn;
-    }
+      for (int e = 0; e < 4; ++e) acc += ez(f[b][e], nm);
+    sum = acc;
+    m = mn;
   }
   Stats st = stats_empty();
   st.mz = m;

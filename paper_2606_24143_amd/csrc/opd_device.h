@@ -361,24 +361,24 @@ __device__ __forceinline__ void stats_add(Stats& s, const typename TI::Vec& xz,
   float vm = fz[0];
 #pragma unroll
   for (int e = 1; e < EPV; ++e) vm = fmaxf(vm, fz[e]);
+  // (while a row's maximum is -inf its terms are 0: offset 0 keeps exp(-inf) =
+  // 0 instead of exp(-inf + inf).  No vector is skipped: the maximum of four
+  // NaN logits is -inf as well, and they have to reach the sum)
   if constexpr (!DENSE) {
     const float mn = fmaxf(s.mz, vm);
-    if (mn != kNegInf) {
-      float acc = s.sz * rescale(s.mz, mn);
-      const float nm = -mn * kLog2e;
+    float acc = s.sz * rescale(s.mz, mn);
+    const float nm = mn != kNegInf ? -mn * kLog2e : 0.f;
 #pragma unroll
-      for (int e = 0; e < EPV; ++e) acc += fast_exp2(fmaf(fz[e], kLog2e, nm));
-      s.sz = acc;
-      s.mz = mn;
-    }
+    for (int e = 0; e < EPV; ++e) acc += fast_exp2(fmaf(fz[e], kLog2e, nm));
+    s.sz = acc;
+    s.mz = mn;
   } else {
     float fy[EPV];
     unpack<TI>(xy, fy);
     float vmy = fy[0];
 #pragma unroll
     for (int e = 1; e < EPV; ++e) vmy = fmaxf(vmy, fy[e]);
-    // each row on its own: while a row's maximum is -inf its terms are 0
-    // (offset 0 keeps exp(-inf) = 0 instead of exp(-inf + inf))
+    // each row on its own
     const float mnz = fmaxf(s.mz, vm), mny = fmaxf(s.my, vmy);
     const float cz = rescale(s.mz, mnz), cy = rescale(s.my, mny);
     float sz = s.sz * cz, tr = s.tr * cz, sy = s.sy * cy, tf = s.tf * cy;

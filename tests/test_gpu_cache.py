@@ -391,6 +391,31 @@ def test_topk_parity(shape, k):
 
 
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+def test_long_stretches_of_nan(dtype):
+    """Scores and supports of rows in which NaN fills the first stretch that a
+    lane reads (its running maximum is still -inf there), all or most of it."""
+    V, N, k = 160_000, 6, 32
+    x = np.random.default_rng(8).normal(0.0, 3.0, (N, V)).astype(np.float32)
+    for r, n in ((0, 8192), (2, 60_000), (4, V)):
+        x[r, :n] = np.nan
+    stored = to_stored(x, dtype)
+    say("long stretches of NaN dtype=%d" % dtype)
+    dev = as_device(stored, V)
+    ids = np.tile(np.array([0, V // 2, V - 1], np.int32), (N, 1))
+    sc = opd.score_actions(dev, to_dev(ids), want_lse=True)
+    tk = opd.topk_support(dev, k, want_lse=True)
+    bare = opd.topk_support(dev, k, want_logp=False)
+    torch.cuda.synchronize()
+    for out in (sc, tk):
+        lse, lp = out["lse"].cpu().numpy(), out["logp"].cpu().numpy()
+        assert np.isnan(lse[::2]).all() and np.isfinite(lse[1::2]).all()
+        assert np.isnan(lp[::2]).all() and np.isfinite(lp[1::2]).all()
+    ref = oracle.cache_rows("topk", dtype, stored, V, k)
+    for out in (tk, bare):
+        assert np.array_equal(out["idx"].cpu().numpy(), ref["ids"])
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
 @pytest.mark.parametrize("case", ["constant", "ties_2000", "ties_5000", "special", "k_eq_v"])
 def test_topk_ties_and_special_values(dtype, case):
     # many equal maxima exercise the LDS sort (over 1024 candidates) and the

@@ -686,6 +686,40 @@ def test_nan_logits_propagate_to_their_row_only():
             assert np.isnan(loss[2]) and np.isfinite(np.delete(loss, 2)).all()
 
 
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+def test_nan_vectors_propagate_wherever_they_lie(dtype):
+    """Whole vectors of NaN (four aligned entries), which leave a lane's running
+    maximum at -inf: as a lane's first vector in memory and as the first one it
+    streams on wide rows, at the row's end, over a long stretch, over the whole
+    row.  Loss and log-partition of the row are NaN, its neighbours' are not."""
+    wide = 80_000 if dtype == synth.F32 else 160_000
+    held = 73_728 if dtype == synth.F32 else 147_456  # entries a wide row keeps in registers
+    for V, est, flags in ((wide, "rkl_mc", opd.FLAG_FORCE_ROWWISE),
+                          (wide, "rkl_topk", opd.FLAG_FORCE_ROWWISE),
+                          (wide, "rkl_mc", opd.FLAG_FORCE_SPLITV),
+                          (wide, "fkl_dense", opd.FLAG_FORCE_SPLITV),
+                          (wide, "fkl_dense", opd.FLAG_FORCE_ROWWISE),
+                          (30_000, "rkl_mc", opd.FLAG_FORCE_ROWWISE),
+                          (30_000, "rkl_mc", opd.FLAG_FORCE_SPLITV)):
+        say("nan vectors V=%d %s flags=%d dtype=%d" % (V, est, flags, dtype))
+        at = [(0, 4), (min(held, V // 2), 4), (V - 4, 4), (V // 4, V // 2), (0, V)]
+        w = synth.Workload("t_nan", N=2 * len(at), V=V, dtype=dtype, estimators=ALL, k=8, M=6,
+                           sigma_student=2.5, sigma_teacher=1.0, sigma_behaviour=0.5,
+                           dense_teacher=True, seed=V)
+        d = synth.generate(w)
+        logits = d["logits"].copy()
+        for i, (a, n) in enumerate(at):
+            logits[2 * i, a:a + n] = np.nan if dtype == synth.F32 else 0x7FC0
+        teacher = to_dev(d["teacher_logits"]) if est in DENSE else None
+        out = run_gpu(to_dev(logits), est, *cache_arrays(d, est), teacher, flags=flags,
+                      want_lse=True)
+        lse, loss = out["lse"].cpu().numpy(), out["loss"].cpu().numpy()
+        assert np.isnan(lse[::2]).all() and np.isfinite(lse[1::2]).all(), lse
+        if est not in TOPK:  # (the renormalised top-k losses read the cached logits only)
+            assert np.isnan(loss[::2]).all(), loss
+        assert np.isfinite(loss[1::2]).all()
+
+
 def test_repeated_calls_are_bitwise_identical():
     w, d, mask = small_inputs("v151936", synth.BF16)
     say("determinism")
