@@ -824,30 +824,58 @@ __global__ void __launch_bounds__(kRowThreads) k_row_dense_resident(Args a) {
 }
 
 // Sweep-1 statistics of vectors [v0, v1) of a row (v0 < v1), one lane's share
-// (stride NT), with B loads of each row in flight per step.
+// (stride NT), with B loads of each row in flight per step: pairs and a last
+// one (B = 2), or steps whose loads are clamped to the range.
 template <class TI, bool DENSE, int NT, int B>
 __device__ __forceinline__ Stats lane_stats(const void* zrow, const void* yrow, int64_t v0,
                                             int64_t v1, int64_t nvec, int tail) {
   constexpr int EPV = TI::EPV;
   Stats s = stats_empty();
-  for (int64_t v = v0 + threadIdx.x; v < v1; v += B * NT) {
-    typename TI::Vec z[B], y[B];
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      if (v - threadIdx.x + b * NT >= v1) break;  // (wave-uniform)
-      const int64_t vb = v + b * NT < v1 ? v + b * NT : v1 - 1;
-      z[b] = ld_cached<TI>(zrow, vb);
-      if constexpr (DENSE) y[b] = ld_cached<TI>(yrow, vb);
-    }
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      if (v + b * NT >= v1) break;
-      if constexpr (!DENSE) y[b] = z[b];
-      if (tail != EPV && v + b * NT == nvec - 1) {
-        mask_tail<TI>(z[b], tail);
-        if constexpr (DENSE) mask_tail<TI>(y[b], tail);
+  if constexpr (B == 2) {
+    int64_t v = v0 + threadIdx.x;
+    for (; v + NT < v1; v += 2 * NT) {
+      typename TI::Vec z0 = ld_cached<TI>(zrow, v), z1 = ld_cached<TI>(zrow, v + NT);
+      typename TI::Vec y0 = z0, y1 = z1;
+      if constexpr (DENSE) {
+        y0 = ld_cached<TI>(yrow, v);
+        y1 = ld_cached<TI>(yrow, v + NT);
       }
-      stats_add<TI, DENSE>(s, z[b], y[b]);
+      if (tail != EPV && v + NT == nvec - 1) {
+        mask_tail<TI>(z1, tail);
+        if constexpr (DENSE) mask_tail<TI>(y1, tail);
+      }
+      stats_add<TI, DENSE>(s, z0, y0);
+      stats_add<TI, DENSE>(s, z1, y1);
+    }
+    if (v < v1) {
+      typename TI::Vec z0 = ld_cached<TI>(zrow, v), y0 = z0;
+      if constexpr (DENSE) y0 = ld_cached<TI>(yrow, v);
+      if (tail != EPV && v == nvec - 1) {
+        mask_tail<TI>(z0, tail);
+        if constexpr (DENSE) mask_tail<TI>(y0, tail);
+      }
+      stats_add<TI, DENSE>(s, z0, y0);
+    }
+  } else {
+    for (int64_t v = v0 + threadIdx.x; v < v1; v += B * NT) {
+      typename TI::Vec z[B], y[B];
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        if (v - threadIdx.x + b * NT >= v1) break;  // (wave-uniform)
+        const int64_t vb = v + b * NT < v1 ? v + b * NT : v1 - 1;
+        z[b] = ld_cached<TI>(zrow, vb);
+        if constexpr (DENSE) y[b] = ld_cached<TI>(yrow, vb);
+      }
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        if (v + b * NT >= v1) break;
+        if constexpr (!DENSE) y[b] = z[b];
+        if (tail != EPV && v + b * NT == nvec - 1) {
+          mask_tail<TI>(z[b], tail);
+          if constexpr (DENSE) mask_tail<TI>(y[b], tail);
+        }
+        stats_add<TI, DENSE>(s, z[b], y[b]);
+      }
     }
   }
   return s;
@@ -1026,16 +1054,25 @@ __global__ void __launch_bounds__(kRowThreads) k_row_stream(Args a) {
 // merges the P records of its row in a fixed order (the same in every chunk
 // of the row, so every chunk sees bit-identical row constants), repeats the
 // K-entry estimator, and writes its chunk of the gradient.
-// Both passes are bound by latency, so a lane requests kSplitAhead vectors at
-// once, in pass 2 before the row's constants are known, beside the chain of
-// cache entries, gathered logits and merge that they come from.  Measured with
-// two, four and eight at V = 151,936 and the chunks of split_plan: 16-sample MC
-// fp32, 63 rows 25.4, 24.1 and 27.4 us; dense bf16, 63 rows 26.7, 25.2 and 26.6
-// (eight hold fewer workgroups on a CU).  At 24 rows, of two or three vectors
-// per lane, it makes no difference: 13.0 us with one at a time as well.
+// Both passes are bound by latency.  Calls that read enough for loads in flight
+// to matter request kSplitAhead vectors per lane at once, in pass 2 before the
+// row's constants are known, beside the chain of cache entries, gathered logits
+// and merge that they come from; the others take them in pairs in pass 1 and one
+// by one in pass 2, whose shorter code is faster there.  Measured with the chunks
+// of split_plan, pairs against ahead: dense fp32 V = 151,936 N = 16 (19 MB) 13.1 /
+// 13.6 us, N = 32 21.4 / 19.6; dense bf16 151,936 N = 24 14.4 / 14.8, N = 63 26.8 /
+// 24.5; dense fp32 65,536 N = 16 10.1 / 10.9; 16-sample MC fp32 151,936 N = 24 14.0 /
+// 13.9, N = 63 26.7 / 24.4.  Up to two vectors per lane a pair holds them all, whatever
+// the call reads: dense fp32 65,536 N = 48 (25 MB) 13.8 / 14.6.
 constexpr int kSplitAhead = 4;
-
 template <class TI, bool DENSE>
+bool split_ahead(const Args& a) {
+  constexpr int64_t bytes = (int64_t)sizeof(typename TI::Vec) * (DENSE ? 2 : 1);
+  return a.N * a.nvec * bytes > (DENSE ? 20 : 16) * 1000000ll &&
+         a.chunk_vec * 5 > 11 * kSplitThreads;  // 2.2 vectors per lane
+}
+
+template <class TI, bool DENSE, int B>
 __global__ void __launch_bounds__(kSplitThreads) k_split_stats(Args a) {
   constexpr int NT = kSplitThreads, NW = NT / 64;
   __shared__ Stats s_red[NW];
@@ -1047,7 +1084,7 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_stats(Args a) {
   const int64_t v1 = v0 + a.chunk_vec < a.nvec ? v0 + a.chunk_vec : a.nvec;
   const void* zrow = (const char*)a.logits + row * a.ld * TI::BYTES;
   const void* yrow = DENSE ? (const char*)a.teacher + row * a.ld * TI::BYTES : nullptr;
-  Stats st = lane_stats<TI, DENSE, NT, kSplitAhead>(zrow, yrow, v0, v1, a.nvec, a.tail);
+  Stats st = lane_stats<TI, DENSE, NT, B>(zrow, yrow, v0, v1, a.nvec, a.tail);
   st = block_merge<DENSE, NW>(st, s_red);
   if (threadIdx.x == 0) {
     float* p = a.ws + ((size_t)row * a.P + chunk) * kPartialFloats;
@@ -1056,9 +1093,9 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_stats(Args a) {
   }
 }
 
-template <class TI, class TO, int EST>
+template <class TI, class TO, int EST, int B>
 __global__ void __launch_bounds__(kSplitThreads) k_split_write(Args a) {
-  constexpr int NT = kSplitThreads, EPV = TI::EPV, B = kSplitAhead;
+  constexpr int NT = kSplitThreads, EPV = TI::EPV;
   constexpr bool DENSE = is_dense(EST);
   __shared__ CacheLds c;
   __shared__ Stats s_row;
@@ -1080,11 +1117,12 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_write(Args a) {
   }
   Stats s = stats_empty();
   if (tid < 64) {
+    if constexpr (B == 1 && !DENSE) load_cache<TI>(a, row, zrow, c);
     if (tid < a.P) {
       const float* p = a.ws + ((size_t)row * a.P + tid) * kPartialFloats;
       s = Stats{p[0], p[1], p[2], p[3], p[4], p[5]};
     }
-    if constexpr (!DENSE) load_cache<TI>(a, row, zrow, c);
+    if constexpr (B > 1 && !DENSE) load_cache<TI>(a, row, zrow, c);
   }
   typename TI::Vec z[B], y[B];
   auto fetch = [&](int b, int64_t vb) {  // the lane's vector of those from vb on
@@ -1093,8 +1131,10 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_write(Args a) {
     if constexpr (DENSE || is_mc(EST)) z[b] = ld_cached<TI>(zrow, v);
     if constexpr (DENSE) y[b] = ld_cached<TI>(yrow, v);
   };
+  if constexpr (B > 1) {
 #pragma unroll
-  for (int b = 0; b < B; ++b) fetch(b, v0 + b * NT);
+    for (int b = 0; b < B; ++b) fetch(b, v0 + b * NT);
+  }
   if (tid < 64) {
     s = wave_merge<DENSE>(s);
     if (tid == 0) s_row = s;
@@ -1104,18 +1144,29 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_write(Args a) {
   const float L = st.mz + logf(st.sz);
   // the chunk's gradient, grad(z, y, v, g) giving that of vector v
   auto write = [&](auto grad) {
-    for (int64_t vb = v0; vb < v1; vb += B * NT) {
-#pragma unroll
-      for (int b = 0; b < B; ++b) {
-        const int64_t v = vb + b * NT + tid;
+    if constexpr (B == 1) {
+      for (int64_t v = v0 + tid; v < v1; v += NT) {
         typename TI::Vec zv{}, yv{};
-        if constexpr (DENSE || is_mc(EST)) zv = z[b];
-        if constexpr (DENSE) yv = y[b];
-        fetch(b, vb + (B + b) * NT);
-        if (v >= v1) continue;
+        if constexpr (DENSE || is_mc(EST)) zv = ld_cached<TI>(zrow, v);
+        if constexpr (DENSE) yv = ld_cached<TI>(yrow, v);
         float g[EPV];
         grad(zv, yv, v, g);
         store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
+      }
+    } else {
+      for (int64_t vb = v0; vb < v1; vb += B * NT) {
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+          const int64_t v = vb + b * NT + tid;
+          typename TI::Vec zv{}, yv{};
+          if constexpr (DENSE || is_mc(EST)) zv = z[b];
+          if constexpr (DENSE) yv = y[b];
+          fetch(b, vb + (B + b) * NT);
+          if (v >= v1) continue;
+          float g[EPV];
+          grad(zv, yv, v, g);
+          store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
+        }
       }
     }
   };
@@ -1405,10 +1456,17 @@ template <class TI, class TO, int EST>
 hipError_t split_t(const Args& a, bool read, hipStream_t s) {
   const dim3 grid((unsigned)(a.N * a.P)), block(kSplitThreads);
   if (!read) return hipErrorInvalidValue;  // the write-only top-k form runs launch_topk_sparse
-  hipLaunchKernelGGL((k_split_stats<TI, is_dense(EST)>), grid, block, 0, s, a);
+  const bool ahead = split_ahead<TI, is_dense(EST)>(a);
+  if (ahead)
+    hipLaunchKernelGGL((k_split_stats<TI, is_dense(EST), kSplitAhead>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_split_stats<TI, is_dense(EST), 2>), grid, block, 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_split_write<TI, TO, EST>), grid, block, 0, s, a);
+  if (ahead)
+    hipLaunchKernelGGL((k_split_write<TI, TO, EST, kSplitAhead>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_split_write<TI, TO, EST, 1>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

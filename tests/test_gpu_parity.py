@@ -297,13 +297,13 @@ def test_resident_row_classes(est, dtype, V):
 
 @pytest.mark.parametrize("dtype,V", [
     (synth.BF16, 65540),   # 256 vectors to a chunk, the last one short
-    (synth.BF16, 262144),  # 1,024: one step of the four vectors a lane requests
-    (synth.F32, 262145),   # one vector in the second step, which the last lacks
-    (synth.BF16, 530001),  # a third step and a partial last vector
+    (synth.BF16, 262144),  # 1,024: two whole pairs per lane
+    (synth.F32, 262145),   # one vector in a third step, which the last lacks
+    (synth.BF16, 530001),  # five steps and a partial last vector
 ])
 @pytest.mark.parametrize("est", ["rkl_mc", "fkl_topk", "rkl_dense"])
 def test_split_chunk_edges(est, dtype, V):
-    """Chunks of the split path whose lanes hold one to three steps of vectors."""
+    """Chunks of the split path whose lanes hold one to nine vectors."""
     ld = (V + 7) // 8 * 8
     w = synth.Workload("t_split", N=3, V=V, dtype=dtype, estimators=ALL, k=16, M=6,
                        sigma_student=2.5, sigma_teacher=1.0, sigma_behaviour=0.5,
@@ -318,6 +318,31 @@ def test_split_chunk_edges(est, dtype, V):
                   want_gathered=est not in DENSE)
     ref = oracle_for(w, d, est, mask, gamma=0.75)
     compare("split/%s/%d" % (est, V), w, d, est, out, ref, mask, gamma=0.75)
+
+
+@pytest.mark.parametrize("est,dtype,N,V", [
+    ("rkl_mc", synth.F32, 41, 100001),     # the fewest bytes; a partial last vector
+    ("fkl_topk", synth.F32, 63, 200002),   # two steps of the vectors a lane requests
+    ("rkl_dense", synth.F32, 40, 100001),  # a second vector in half of the lanes
+    ("fkl_dense", synth.BF16, 63, 100003),
+])
+def test_split_requests_ahead(est, dtype, N, V):
+    """Split calls that read enough to request several vectors per lane ahead."""
+    ld = (V + 7) // 8 * 8
+    w = synth.Workload("t_ahead", N=N, V=V, dtype=dtype, estimators=ALL, k=16, M=6,
+                       sigma_student=2.5, sigma_teacher=1.0, sigma_behaviour=0.5,
+                       dense_teacher=est in DENSE, seed=V)
+    d = synth.generate(w, ld=ld)
+    mask = np.ones(N, np.uint8)
+    mask[1::7] = 0
+    say("ahead %s N=%d V=%d" % (est, N, V))
+    teacher = to_dev(d["teacher_logits"])[:, :V] if est in DENSE else None
+    ids, tau, beta = cache_arrays(d, est)
+    out = run_gpu(to_dev(d["logits"])[:, :V], est, ids, tau, beta, teacher, mask=mask,
+                  grad_scale=0.75, flags=opd.FLAG_FORCE_SPLITV, want_lse=True,
+                  want_gathered=est not in DENSE)
+    ref = oracle_for(w, d, est, mask, gamma=0.75)
+    compare("ahead/%s/%d" % (est, V), w, d, est, out, ref, mask, gamma=0.75)
 
 
 @pytest.mark.parametrize("N,V", [(1, 32768), (63, 32768), (1, 32776), (24, 32772), (63, 32772),
