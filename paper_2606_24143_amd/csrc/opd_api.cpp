@@ -23,11 +23,21 @@ using opd::Path;
 constexpr int64_t kSplitMaxRows = 64;
 // Workgroups the split path aims for below kSplitMaxRows: six to a CU, all of
 // them resident at once (two or three rounds of shorter ones repeat the rows'
-// merge and estimator in each).  Against 8,192 (64 chunks per row, as before),
-// V = 151,936: bf16 MC N = 48: 17.9 against 21.2 us; 63: 19.6 against 24.6;
-// fp32 63: 24.1 / 30.9; dense bf16 63: 25.2 / 31.4; V = 60,000 48: 13.1 / 18.7.
-// 512 and 1,024: 23.4 and 22.2 us where 1,536 takes 19.6.
+// merge and estimator in each).  Against 8,192 (64 chunks per row), V = 151,936:
+// bf16 MC N = 48: 17.5 against 20.4 us; 63: 19.9 / 24.0; fp32 63: 24.5 / 30.4;
+// dense bf16 63: 24.5 / 29.6; V = 60,000 48: 13.1 / 18.7.  512 and 1,024: 23.4
+// and 22.2 us where 1,536 takes 19.6; 2,048: 23.5.
 constexpr int64_t kSplitResidentGroups = 1536;
+// Two kinds of calls keep 64 chunks.  Those that read more than the caches hold
+// between the passes are bound by memory, where more and shorter workgroups
+// leave less idle at the end: dense fp32 V = 300,000 N = 40 (96 MB): 45.3 against 47.2
+// us, 63: 64.7 / 67.4; 250,000 56: 48.8 / 52.5; but 151,936 63 (77 MB): 37.3 / 36.5.  And
+// up to 32 rows whose chunks are then four to five vectors per lane, of 2-byte
+// logits or an estimator that writes without reading again: their 2,048 workgroups
+// (eight to a CU) are all resident too, and 48 chunks would take six or seven
+// vectors: bf16 MC V = 262,144 N = 32: 17.8 / 19.4, 300,000: 19.6 / 21.2; fp32 top-k with
+// the log-partition 262,144: 19.4 / 20.8; but bf16 MC 400,000: 25.4 / 24.2.
+constexpr int64_t kSplitResidentBytes = 78000000;
 // The workspace's size, and the chunks of forced calls over more rows, come
 // from this target and the largest chunk count.
 constexpr int64_t kSplitTargetGroups = 8192;
@@ -98,10 +108,11 @@ struct Plan {
 };
 
 // The split-path layout for N rows of nvec vectors: enough chunks for about
-// kSplitTargetGroups workgroups (kSplitResidentGroups below kSplitMaxRows
-// rows), each chunk at least one vector per lane.  The workspace is sized for
-// the former, so a size that serves some rows serves fewer.
-Plan split_plan(int64_t N, int64_t nvec) {
+// kSplitTargetGroups workgroups (kSplitResidentGroups below kSplitMaxRows rows,
+// but see there), each chunk at least one vector per lane.  The workspace is
+// sized for the former, so a size that serves some rows serves fewer.
+Plan split_plan(int64_t N, int64_t nvec, int32_t dtype, int32_t est) {
+  const int vec_bytes = elems_per_vec(dtype) * elt_bytes(dtype) * (est_dense(est) ? 2 : 1);
   Plan p{true, 1, nvec, 0};
   int64_t P = (kSplitTargetGroups + N - 1) / N;
   const int64_t by_width = nvec / opd::kSplitThreads;
@@ -110,7 +121,11 @@ Plan split_plan(int64_t N, int64_t nvec) {
   if (P < 1) P = 1;
   p.ws_bytes = (size_t)N * (size_t)P * opd::kPartialFloats * sizeof(float);
   const int64_t resident = (kSplitResidentGroups + N - 1) / N;
-  if (N < kSplitMaxRows && P > resident) P = resident;
+  const int64_t one = kSplitMaxChunks * opd::kSplitThreads;  // vectors of one per lane
+  const bool many = N * nvec * vec_bytes > kSplitResidentBytes ||
+                    (N <= kSplitMaxRows / 2 && nvec >= 4 * one && nvec <= 5 * one &&
+                     (est_topk(est) || (dtype == OPD_BF16 && !est_dense(est))));
+  if (N < kSplitMaxRows && !many && P > resident) P = resident;
   p.P = (int)P;
   p.chunk_vec = (nvec + P - 1) / P;
   return p;
@@ -283,7 +298,7 @@ size_t opd_workspace_bytes(int64_t N, int64_t V, int32_t dtype, int32_t estimato
   if (check_shape(N, V, V) != OPD_OK || N == 0) return 0;
   if (check_support(estimator, V, k, M) != OPD_OK || check_flags(flags) != OPD_OK) return 0;
   if (!split_wanted(N, flags)) return 0;
-  return split_plan(N, nvec_of(V, dtype)).ws_bytes;
+  return split_plan(N, nvec_of(V, dtype), dtype, estimator).ws_bytes;
 }
 
 int opd_loss_fwd_bwd(const void* logits, int32_t dtype, int64_t N, int64_t V, int64_t ld,
@@ -353,7 +368,7 @@ int loss_call(const void* logits, int32_t dtype, int64_t N, int64_t V, int64_t l
 
   Plan plan{false, 1, nvec, 0};
   if (split_wanted(N, o.flags) && !narrow) {
-    const Plan sp = split_plan(N, nvec);
+    const Plan sp = split_plan(N, nvec, dtype, estimator);
     if (scratch) {
       // the no-allocation entry point: the library's static scratch array,
       // looked up only now that every argument has been checked

@@ -1063,13 +1063,16 @@ __global__ void __launch_bounds__(kRowThreads) k_row_stream(Args a) {
 // 13.6 us, N = 32 21.4 / 19.6; dense bf16 151,936 N = 24 14.4 / 14.8, N = 63 26.8 /
 // 24.5; dense fp32 65,536 N = 16 10.1 / 10.9; 16-sample MC fp32 151,936 N = 24 14.0 /
 // 13.9, N = 63 26.7 / 24.4.  Up to two vectors per lane a pair holds them all, whatever
-// the call reads: dense fp32 65,536 N = 48 (25 MB) 13.8 / 14.6.
+// the call reads: dense fp32 65,536 N = 48 (25 MB) 13.8 / 14.6; and where the grid
+// leaves most of the chip idle nothing is gained: dense fp32 400,000 N = 8 (512
+// workgroups) 14.4 / 14.8.
 constexpr int kSplitAhead = 4;
 template <class TI, bool DENSE>
 bool split_ahead(const Args& a) {
   constexpr int64_t bytes = (int64_t)sizeof(typename TI::Vec) * (DENSE ? 2 : 1);
   return a.N * a.nvec * bytes > (DENSE ? 20 : 16) * 1000000ll &&
-         a.chunk_vec * 5 > 11 * kSplitThreads;  // 2.2 vectors per lane
+         a.chunk_vec * 5 > 11 * kSplitThreads &&  // 2.2 vectors per lane
+         a.N * a.P >= 1024;
 }
 
 template <class TI, bool DENSE, int B>

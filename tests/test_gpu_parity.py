@@ -346,7 +346,7 @@ def test_split_requests_ahead(est, dtype, N, V):
 
 
 @pytest.mark.parametrize("N,V", [(1, 32768), (63, 32768), (1, 32776), (24, 32772), (63, 32772),
-                                 (63, 151933)])
+                                 (63, 151933), (31, 262145), (33, 262145), (31, 327684)])
 def test_few_rows_choose_their_path(N, V):
     """The widest row that stays whole below 64 rows, and split ones at the
     row counts where the chunks change."""
