@@ -137,6 +137,33 @@ bool split_wanted(int64_t N, uint32_t flags) {
   return N < kSplitMaxRows;
 }
 
+// Below kSplitMaxRows rows, those that stay whole: the register-resident
+// kernel's classes that share a CU, one launch of one read, where its longer
+// chain (a lane's slots, then the cache entries, which one wave handles while the
+// others wait) is no longer than the split path's two launches.
+// Measured, split against row path, Monte-Carlo with K draws: K = 1 bf16 V = 16,384
+// N = 8: 7.3 / 7.0 us, 24,576 8: 7.4 / 7.6; K = 16 bf16 2,000 8: 9.6 / 6.1, 12,000 8: 9.0 /
+// 8.2, 16,384 8: 8.0 / 8.5 and 63: 10.8 / 9.5, 32,768 8: 8.1 / 9.7 and 24: 9.7 / 9.6; fp32
+// 16,384 8: 7.9 / 6.9; K = 32 bf16 4,096 8: 8.4 / 8.0, 8,192 63: 9.5 / 10.3, 32,768 8: 8.4 /
+// 10.7 and 63: 14.2 / 11.3; fp32 8,192 8: 8.3 / 9.0, 16,384 24: 8.9 / 8.7; K = 48 bf16 2,000
+// (one chunk) 8: 10.7 / 9.5, 4,096 8: 8.8 / 9.8, 32,768 63: 14.9 / 13.1; K = 64 bf16 4,096 8:
+// 9.1 / 11.2, 24,576 63: 13.7 / 14.5; K = 128 bf16 8,192 8: 13.3 / 21.6.  The renormalised
+// top-k with the log-partition, K = 32: fp32 2,000 8: 10.3 / 8.8, 8,192 8: 8.6 / 9.2, 16,384
+// 63: 11.9 / 11.2; bf16 16,384 8: 8.7 / 10.1.  Wider rows, K = 16, 60,000 8: 9.5 / 11.7;
+// dense rows have no such class: V = 32,000 63: 13.0 / 16.3.
+bool whole_rows(int64_t N, int64_t nvec, int32_t dtype, int32_t est, int K, uint32_t flags) {
+  if ((flags & OPD_FLAG_FORCE_SPLITV) || est_dense(est)) return false;
+  const int64_t slots = opd::slots_small(dtype);
+  if (nvec > slots * (opd::kRowThreads / 2)) return false;
+  const bool f32 = dtype == OPD_F32;
+  const bool wide = nvec > slots * (opd::kRowThreads / 4);  // 512 lanes to a row
+  if (est_topk(est)) return f32 && K <= 32 && (nvec <= 512 || (wide && N >= 56));
+  if (K <= 8) return f32 || nvec <= 4096 || N >= 24;
+  if (K <= 16) return f32 || nvec <= 3072 || N >= (wide ? 24 : 32);
+  if (K <= 32) return nvec <= 1024 || (wide && (f32 || N >= 40));
+  return K <= 48 && ((nvec > 256 && nvec <= 512) || (wide && N >= 56));
+}
+
 int64_t nvec_of(int64_t V, int32_t dt) {
   const int64_t epv = elems_per_vec(dt);
   return (V + epv - 1) / epv;
@@ -357,17 +384,8 @@ int loss_call(const void* logits, int32_t dtype, int64_t N, int64_t V, int64_t l
   const int epv = elems_per_vec(dtype);
   const int tail = (int)(V - (nvec - 1) * epv);
 
-  // Rows of the register-resident kernel's classes that share a CU take it
-  // whatever N is: one launch of one read.  Measured, split against row path,
-  // 16-sample MC: V = 20,000 bf16 N = 8: 9.2 against 8.8 us; 63: 11.9 / 9.4; V
-  // = 32,000 N = 24: 11.3 / 9.6; 63: 15.0 / 10.0.  Wider ones are split: V =
-  // 60,000 N = 8: 9.5 / 11.7.  (Dense rows have no such class: V = 32,000 N =
-  // 63: 13.0 / 16.3.)
-  const bool narrow = !est_dense(estimator) && !(o.flags & OPD_FLAG_FORCE_SPLITV) &&
-                      nvec <= (int64_t)opd::slots_small(dtype) * (opd::kRowThreads / 2);
-
   Plan plan{false, 1, nvec, 0};
-  if (split_wanted(N, o.flags) && !narrow) {
+  if (split_wanted(N, o.flags) && !whole_rows(N, nvec, dtype, estimator, K, o.flags)) {
     const Plan sp = split_plan(N, nvec, dtype, estimator);
     if (scratch) {
       // the no-allocation entry point: the library's static scratch array,

@@ -345,17 +345,27 @@ def test_split_requests_ahead(est, dtype, N, V):
     compare("ahead/%s/%d" % (est, V), w, d, est, out, ref, mask, gamma=0.75)
 
 
-@pytest.mark.parametrize("N,V", [(1, 32768), (63, 32768), (1, 32776), (24, 32772), (63, 32772),
-                                 (63, 151933), (31, 262145), (33, 262145), (31, 327684)])
-def test_few_rows_choose_their_path(N, V):
-    """The widest row that stays whole below 64 rows, and split ones at the
-    row counts where the chunks change."""
+@pytest.mark.parametrize("dtype,N,V,M", [
+    (synth.BF16, 56, 32768, 16), (synth.BF16, 56, 32768, 48), (synth.BF16, 55, 32768, 48),
+    (synth.BF16, 24, 32768, 16), (synth.BF16, 23, 32768, 8), (synth.BF16, 39, 16388, 32),
+    (synth.BF16, 40, 16388, 32), (synth.BF16, 31, 16384, 16), (synth.BF16, 32, 16384, 16),
+    (synth.BF16, 2, 16384, 8), (synth.BF16, 2, 12288, 16), (synth.BF16, 2, 12289, 16),
+    (synth.BF16, 5, 4096, 32), (synth.BF16, 5, 4097, 32), (synth.F32, 5, 8192, 32),
+    (synth.F32, 5, 8193, 32), (synth.F32, 5, 16385, 16), (synth.F32, 5, 1025, 48),
+    (synth.F32, 5, 1024, 48), (synth.F32, 5, 2048, 48), (synth.F32, 5, 2049, 49),
+    (synth.BF16, 1, 32776, 16), (synth.BF16, 63, 32772, 16),
+    (synth.BF16, 63, 151933, 16), (synth.BF16, 31, 262145, 16), (synth.BF16, 33, 262145, 16),
+    (synth.BF16, 31, 327684, 16)])
+def test_few_rows_choose_their_path(dtype, N, V, M):
+    """Rows that stay whole below 64 rows and those that are split, on both
+    sides of each line between them (rows, width, draws, type), and split ones
+    at the row counts where the chunks change."""
     ld = (V + 7) // 8 * 8
-    w = synth.MC16.replace(N=N, V=V, M=16, seed=N + V)
+    w = synth.MC16.replace(N=N, V=V, M=M, seed=N + V, dtype=dtype)
     d = synth.generate(w, ld=ld)
     mask = np.ones(N, np.uint8)
     mask[1::5] = 0
-    say("few rows N=%d V=%d" % (N, V))
+    say("few rows N=%d V=%d M=%d" % (N, V, M))
     ids, tau, beta = cache_arrays(d, "rkl_mc")
     out = run_gpu(to_dev(d["logits"])[:, :V], "rkl_mc", ids, tau, beta, mask=mask,
                   grad_scale=0.5, want_lse=True, want_gathered=True)
