@@ -217,8 +217,9 @@ typedef struct opd_opts {
  *                 OPD_ERR_PARAM); for the renormalised ones it adds one read
  *                 of the logits, as lse_out does.
  *   workspace     device scratch for the split-vocabulary path, nullable;
- *   workspace_bytes  its size.  The split path is taken for small N (or when
- *                 forced) only if workspace_bytes >= opd_workspace_bytes(...);
+ *   workspace_bytes  its size.  The split path is taken for small N (unless the
+ *                 rows are narrow enough to be faster whole) or when forced,
+ *                 and only if workspace_bytes >= opd_workspace_bytes(...);
  *                 otherwise the row-per-workgroup path runs.
  *   stream        hipStream_t to launch on (NULL = default stream)
  * Returns OPD_OK or an opd_status error.  N == 0 is a no-op returning OPD_OK.
@@ -262,10 +263,13 @@ int opd_loss_fwd_bwd_noalloc(const void* logits, int32_t dtype, int64_t N, int64
 size_t opd_noalloc_scratch_bytes(void);
 
 /*
- * Bytes of workspace opd_loss_fwd_bwd uses for these arguments (0 when the
- * call takes the row-per-workgroup path): the split-vocabulary path's
- * per-(row, chunk) statistics records, N * P * 32 bytes.  Pure host function:
- * the answer depends only on its arguments.  Invalid arguments return 0.
+ * Bytes of workspace that let opd_loss_fwd_bwd take the split-vocabulary path
+ * for these arguments: its per-(row, chunk) statistics records, N * P * 32
+ * bytes, for calls below 64 rows or with OPD_FLAG_FORCE_SPLITV, else 0.  The
+ * records need not all be used, and a call may not need them: narrow rows and
+ * write-only top-k calls below 64 rows run the row-per-workgroup path, and
+ * leave the workspace as it is, with or without one.  Pure host function: the
+ * answer depends only on its arguments.  Invalid arguments return 0.
  */
 size_t opd_workspace_bytes(int64_t N, int64_t V, int32_t dtype, int32_t estimator, int32_t k,
                            int32_t M, uint32_t flags);

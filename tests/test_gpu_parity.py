@@ -708,6 +708,28 @@ def test_prepared_call_repeats_the_call(est):
             assert torch.equal(res[key], ref[key]), key
 
 
+@pytest.mark.parametrize("est,N,V,M,flags,split", [
+    ("rkl_mc", 48, 2000, 16, 0, False),     # narrow rows stay whole
+    ("rkl_mc", 48, 2000, 16, opd.FLAG_FORCE_SPLITV, True),
+    ("rkl_mc", 8, 32768, 16, 0, True),
+    ("rkl_mc", 8, 40000, 16, 0, True),
+    ("rkl_mc", 8, 40000, 16, opd.FLAG_FORCE_ROWWISE, False),
+    ("fkl_topk", 8, 40000, 16, 0, False),   # only the cached logits are read
+])
+def test_a_workspace_is_written_by_the_split_path_only(est, N, V, M, flags, split):
+    """What opd.h says of opd_workspace_bytes: the size is reported for calls
+    below 64 rows, and a call that stays whole leaves the workspace alone."""
+    w = synth.MC16.replace(N=N, V=V, M=M, k=M, seed=V)
+    d = synth.generate(w)
+    say("workspace %s N=%d V=%d flags=%d" % (est, N, V, flags))
+    nb = opd.workspace_bytes(N, V, w.dtype, est, M, M, flags)
+    assert (nb > 0) == (flags != opd.FLAG_FORCE_ROWWISE)
+    ws = torch.full((max(nb, 4096),), 0xA5, dtype=torch.uint8, device=DEV)
+    run_gpu(to_dev(d["logits"]), est, *cache_arrays(d, est), flags=flags, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((ws != 0xA5).any()) == split
+
+
 def test_nan_logits_propagate_to_their_row_only():
     w, d, _ = small_inputs("v1000", synth.F32)
     logits = d["logits"].copy()
