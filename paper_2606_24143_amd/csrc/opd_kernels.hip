@@ -891,7 +891,8 @@ __device__ __forceinline__ Stats lane_stats(const void* zrow, const void* yrow, 
 // re-read is what is over the row's own bytes.  Measured against both sweeps
 // from memory, fp32 rows of 151,936: 1,024 rows with 64 draws 250 us against
 // 336, 4,096 with 16 906 against 1,325; bf16 rows of 300,000, 512 rows: 202
-// against 239.
+// against 239.  The renormalised top-k, which reads nothing again, gains from the
+// register slots' early requests alone (row_t says where).
 constexpr int kWideVgprs = 72;
 constexpr int kWideAhead = 4;
 
@@ -919,7 +920,7 @@ __global__ void __launch_bounds__(kRowThreads) k_row_wide(Args a) {
     for (uint32_t i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(32);
   }
   if (tid < 64) load_cache<TI>(a, row, zrow, c);
-  const uint32_t nvec = (uint32_t)a.nvec;  // > NR * NT (wide_row)
+  const uint32_t nvec = (uint32_t)a.nvec;  // > NR * NT: the resident kernel holds the others
   const bool ragged = a.tail != EPV;
   Vec x[NR];
 #pragma unroll
@@ -1015,36 +1016,67 @@ __global__ void __launch_bounds__(kRowThreads) k_row_wide(Args a) {
   }
 }
 
-// One 1024-lane workgroup per row, streaming two rows: sweep 1 reads them,
-// sweep 2 reads them again (plain loads, so the second read can hit L2 or the
-// Infinity Cache).  For the dense estimators on rows wider than
-// k_row_dense_resident holds.
+// One 1024-lane workgroup per row, streaming: sweep 1 reads the row(s), sweep 2
+// reads them again (plain loads, so the second read can hit L2 or the Infinity
+// Cache).  For the dense estimators, which read two rows, on rows wider than
+// k_row_dense_resident holds, and for the other estimators' wide rows where two
+// small workgroups to a CU beat one that keeps the row (row_t).
 template <class TI, class TO, int EST>
 __global__ void __launch_bounds__(kRowThreads) k_row_stream(Args a) {
   constexpr int NT = kRowThreads, NW = NT / 64, EPV = TI::EPV;
-  static_assert(is_dense(EST), "the other estimators' wide rows take k_row_wide");
+  constexpr bool DENSE = is_dense(EST);
   __shared__ Stats s_red[NW];
+  __shared__ CacheLds c;
   const int tid = threadIdx.x;
   const int64_t row = xcd_remap(blockIdx.x, gridDim.x);
   const void* zrow = (const char*)a.logits + row * a.ld * TI::BYTES;
-  const void* yrow = (const char*)a.teacher + row * a.ld * TI::BYTES;
+  const void* yrow = DENSE ? (const char*)a.teacher + row * a.ld * TI::BYTES : nullptr;
   void* grow = (char*)a.dlogits + row * a.ld * TO::BYTES;
   if (a.mask && a.mask[row] == 0) {
     masked_row<TI, TO, NT>(a, row, grow, 0, a.nvec, true);
     return;
   }
-  Stats st = lane_stats<TI, true, NT, 2>(zrow, yrow, 0, a.nvec, a.nvec, a.tail);
-  st = block_merge<true, NW>(st, s_red);
-  const DenseRow d = dense_row<EST>(st);
-  if (tid == 0) {
-    a.loss[row] = d.loss;
-    if (a.lse_out) a.lse_out[row] = d.Lz;
+  if constexpr (!DENSE) {
+    for (int w = tid; w < kFilterWords; w += NT) c.filter[w] = 0u;
+    if (tid < 64) load_cache<TI>(a, row, zrow, c);
   }
-  const DenseGrad dk = dense_grad_consts(d, a.gamma);
-  for (int64_t v = tid; v < a.nvec; v += NT) {
-    float g[EPV];
-    dense_grad<TI, EST>(ld_cached<TI>(zrow, v), ld_cached<TI>(yrow, v), dk, g);
-    store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
+  Stats st = lane_stats<TI, DENSE, NT, 2>(zrow, yrow, 0, a.nvec, a.nvec, a.tail);
+  st = block_merge<DENSE, NW>(st, s_red);
+  if constexpr (DENSE) {
+    const DenseRow d = dense_row<EST>(st);
+    if (tid == 0) {
+      a.loss[row] = d.loss;
+      if (a.lse_out) a.lse_out[row] = d.Lz;
+    }
+    const DenseGrad dk = dense_grad_consts(d, a.gamma);
+    for (int64_t v = tid; v < a.nvec; v += NT) {
+      float g[EPV];
+      dense_grad<TI, EST>(ld_cached<TI>(zrow, v), ld_cached<TI>(yrow, v), dk, g);
+      store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
+    }
+  } else {
+    const float L = st.mz + logf(st.sz);
+    if (tid < 64) finish_row<TI, EST>(a, row, L, true, c);
+    __syncthreads();
+    const bool bad = c.bad != 0;
+    const float C = c.C, nL = -L * kLog2e;
+    for (int64_t v = tid; v < a.nvec; v += NT) {
+      float g[EPV];
+      if constexpr (is_mc(EST)) {
+        float f[EPV];
+        unpack<TI>(ld_cached<TI>(zrow, v), f);
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) g[e] = C * fast_exp2(fmaf(f[e], kLog2e, nL));
+      } else {
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) g[e] = 0.f;
+      }
+      apply_spikes<EPV>(v, g, a.K, c);
+      if (bad)
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) g[e] = __builtin_nanf("");
+      store_vec<TI, TO>(grow, v, g, v == a.nvec - 1 ? a.tail : EPV);
+    }
   }
 }
 
@@ -1449,7 +1481,26 @@ hipError_t row_t(const Args& a, Path path, bool read, hipStream_t s) {
     } else if (path != Path::RowStream) {
       return resident_t<TI, TO, EST>(a, s);
     } else {
-      hipLaunchKernelGGL((k_row_wide<TI, TO, EST>), grid, block, 0, s, a);
+      // k_row_wide has one workgroup to a CU, k_row_stream two.  The Monte-Carlo
+      // family takes the former, except bf16 rows that start between cache lines
+      // and stay in the caches between the sweeps, where a short second round
+      // would run: V = 200,001, 16 draws, k_row_stream against k_row_wide: N = 256 85.4 / 80.1
+      // us, 257 91.2 / 98.9, 272 99.8 / 108.0, 300 105.8 / 111.5, 340 117.3 / 115.5; aligned,
+      // V = 160,000, 257: 70.1 / 68.0; wider, 300,000, 257: 155 / 137.  The renormalised top-k
+      // with the log-partition takes it for one round, and for fp32 rows where neither
+      // kernel's last round is short: V = 160,000 bf16 N = 64: 34.2 / 31.8, 256: 42.0 / 39.3, 300:
+      // 52.8 / 65.1; 200,001 2,048: 403 / 448; fp32 100,003 300: 54.3 / 57.5, 1,024: 140.3 / 134.2,
+      // 2,048: 266 / 274.
+      constexpr bool BF = TI::BYTES == 2;
+      bool wide;
+      if constexpr (is_mc(EST))
+        wide = !(BF && a.N > 256 && a.N <= 320 && a.ld % 64 != 0 && a.nvec <= 54 * kRowThreads);
+      else
+        wide = a.N <= 256 || (!BF && a.N > 512 && a.N <= 1536);
+      if (wide)
+        hipLaunchKernelGGL((k_row_wide<TI, TO, EST>), grid, block, 0, s, a);
+      else if constexpr (!is_mc(EST) || BF)
+        hipLaunchKernelGGL((k_row_stream<TI, TO, EST>), grid, block, 0, s, a);
     }
   }
   return hipGetLastError();

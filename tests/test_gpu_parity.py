@@ -273,6 +273,33 @@ def test_wide_rows(est, dtype, V, ld):
                 bf16_out=out_dt == torch.bfloat16)
 
 
+@pytest.mark.parametrize("est,V,N", [("rkl_mc", 155653, 257), ("fkl_topk_trunc", 200001, 257),
+                                     ("rkl_mc", 155653, 256), ("rkl_topk", 155653, 257)])
+def test_wide_rows_past_one_round(est, V, N):
+    """Wide bf16 rows between cache lines, where the rows past the 256th choose
+    the streaming kernel."""
+    ld = (V + 7) // 8 * 8
+    w = synth.MC16.replace(N=N, V=V, M=16, k=16, seed=V)
+    d = synth.generate(w, ld=ld)
+    mask = np.ones(N, np.uint8)
+    mask[1::4] = 0
+    say("past one round %s V=%d N=%d" % (est, V, N))
+    ids, tau, beta = cache_arrays(d, est)
+    ids = ids.copy()
+    ids[8, 1] = V  # (a row of NaN)
+    out = run_gpu(to_dev(d["logits"])[:, :V], est, ids, tau, beta, mask=mask, grad_scale=0.5,
+                  want_lse=True, want_gathered=True)
+    assert torch.isnan(out["dlogits"][8]).all() and bool(torch.isnan(out["loss"][8]))
+    rows = np.array([r for r in range(N) if r != 8 and (r < 12 or r % 16 == 0 or r == N - 1)])
+    ref = oracle.rows(est, oracle_dtype(w.dtype), d["logits"][rows], V, ids=ids[rows],
+                      tau=tau[rows], beta=None if beta is None else beta[rows], mask=mask[rows],
+                      gamma=0.5)
+    sub = {k: t[torch.from_numpy(rows).to(DEV)] for k, t in out.items()}
+    d = {k: (v[rows] if isinstance(v, np.ndarray) and v.shape[:1] == (N,) else v)
+         for k, v in d.items()}
+    compare("round/%s/%d" % (est, V), w, d, est, sub, ref, mask[rows], gamma=0.5)
+
+
 @pytest.mark.parametrize("dtype,V", [
     (dt, V + d)
     for dt, widths in ((synth.BF16, (4096, 16384, 32768, 65536, 98304, 126976, 155648)),
