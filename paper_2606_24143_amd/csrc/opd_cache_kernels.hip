@@ -756,19 +756,28 @@ __global__ void __launch_bounds__(kSmpThreads) k_sample(CacheArgs a) {
 }
 
 // ---------------------------------------------------------------- draws of bf16 rows
-// A bf16 logit has few values: 23 binades of magnitude [2^-17, 64), both
-// signs, are 5,888.  k_sample_tab keeps exp(z) of each, in double, in LDS, so
-// the term of an element is one LDS read, and the pass over the row one integer
-// sequence and one double addition per element where the exponential takes
-// sixteen double-precision instructions; and the terms exp(z), not exp(z -
-// max), need no maximum.  The entries are within about 3.4e-16 relative
-// (exp_reduced: 1.5e-15).  A tile that holds any other value is summed by
-// term_any: magnitudes below 2^-17 by exp's series, logits below -820 (-inf
-// among them) as 0.  A row with any other value (a NaN, 64 or more, [-820,
-// -64]), or whose sum is below exp(-60), is marked for k_sample_redo.  In the
-// rows that stay every term that is not 0 is above exp(-64), and the row's
-// maximum is above -74 (its sum is at most V exp(max)), so a logit below -820
-// is 0 in double's exp(z - max) as well.
+// A bf16 logit has few values: those of magnitude [2^-17, 640), both signs, are
+// 6,720.  k_sample_tab keeps exp(z) of each, in double, in LDS, so the term of an
+// element is one LDS read, and the pass over the row one integer sequence and
+// one double addition per element where the exponential takes sixteen
+// double-precision instructions; and the terms exp(z), not exp(z - max), need no
+// maximum.  The entries are within about 3.4e-16 relative (exp_reduced:
+// 1.5e-15).  A tile that holds a value outside [2^-17, 352) classes its elements
+// by their offsets, two to an instruction: logits below -820 (-inf among them) read
+// the entry past the table, 0; zeros are counted; other magnitudes below 2^-17
+// take exp's series.  A row with any other value ([640, inf), [-820, -640]), or
+// whose sum is below exp(-60), is marked for k_sample_redo; one with a NaN or
+// +inf has no distribution.  In the rows that stay the maximum is above -74 (the
+// sum is at most V exp(max)), so a logit below -820 is 0 in double's exp(z - max)
+// as well.  Where all magnitudes are below 352 no term that is not 0 would
+// underflow there either; in the other ("far") rows one may, which can matter to
+// a uniform of 0 only (any other is at least 2^-149 of the sum), so a far row that
+// has one is marked too.
+// Measured at 4,096 rows of V = 151,936, 16 draws each, against k_sample for every
+// row: a tenth of the entries -inf 309 / 443 us, nine tenths 295 / 410, a tenth zeros
+// 394 / 430, one entry of 400 in every row 217 / 440, one of NaN 205 / 395; but one of 700
+// in every row (both kernels read it) 612 / 446, and every entry below 2^-17 and not 0
+// 654 / 405.
 //
 // One 1,024-lane workgroup per CU stays for all its rows, so the table is set
 // up once, and its 16 waves take work from one queue: for each row its tiles
@@ -778,9 +787,12 @@ __global__ void __launch_bounds__(kSmpThreads) k_sample(CacheArgs a) {
 // in a ring of slots.  A wave only ever waits for items before its own in the
 // queue (a draw for its row's tiles, a tile for the draws of the row that held
 // its slot), all of them held by running waves, so every wait ends.
-// Measured at 4,096 rows of V = 151,936, 16 draws each: 222 us (5.6 TB/s; a
+// Measured at 4,096 rows of V = 151,936, 16 draws each: 220 us (5.7 TB/s; a
 // plain read of the rows takes 183), against 430-450 us for k_sample, and 258
-// us with a workgroup, and a table, per row.
+// us with a workgroup, and a table, per row; 256 rows 29.4 / 53.5, 2,048 rows of V =
+// 20,000 43.2 / 65.  (The draws of chunks with unusual values are found one by one
+// after the others, and the sums keep to the registers left: four copies of
+// the former, or an element's rare term beside each read, spill into the stream.)
 constexpr int kTabThreads = 1024;
 constexpr int kTabRing = 2560;                  // records in the ring
 constexpr int kTabMaxSlots = 8;
@@ -789,12 +801,14 @@ constexpr int64_t kTabMinVec = 4096;
 constexpr int kTabCus = 256;
 constexpr int kTabDraws = 4;                    // draws per item
 constexpr uint32_t kTabLoExp = 110;             // biased exponent of 2^-17
-constexpr uint32_t kTabHiExp = 133;             // and of 64
 constexpr uint32_t kTabBase = kTabLoExp << 7;   // bf16 magnitude bits of 2^-17
-constexpr uint32_t kTabSize = (kTabHiExp - kTabLoExp) * 256;
-static_assert(kTabSize * 8 <= 65536, "a table offset in bytes has 16 bits");
-constexpr float kTabTiny = 7.62939453125e-06f;  // 2^-17
-constexpr float kTabZero = -820.f;
+constexpr uint32_t kTabEnd = 0x4420;            // of 640
+constexpr uint32_t kTabFar = 0x43B0;            // and of 352
+constexpr uint32_t kTabSize = 2 * (kTabEnd - kTabBase);
+constexpr uint32_t kTabNear = 2 * (kTabFar - kTabBase);  // the fast path's entries
+constexpr uint32_t kTabBinades = (kTabSize + 255) / 256;
+static_assert(kTabSize % 32 == 0, "the table ends with a whole set of low factors");
+static_assert((kTabSize + 1) * 8 <= 65536, "a table offset in bytes has 16 bits");
 constexpr double kTabMinSum = 8.75651076269652e-27;  // exp(-60)
 // ids_out[row * M] of a row left to k_sample_redo
 constexpr int32_t kSampleRedo = -2;
@@ -802,26 +816,28 @@ constexpr int32_t kSampleRedo = -2;
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 struct TabLds {
-  double e[kTabSize];  // exp(z), z's magnitude and sign bit (rotated to the lowest) as index
+  // exp(z), z's magnitude and sign bit (rotated to the lowest) as index; then 0
+  double e[kTabSize + 2];
   union {
     struct {
       double s[kTabRing];  // chunk sums
       double p[kTabRing];  // their inclusive prefix
     };
-    double lo[kTabSize / 8];  // the table's low factors, while it is set up
+    double lo[kTabBinades * 32];  // the table's low factors, while it is set up
   };
   uint32_t next;                   // the queue: the next item
   uint32_t done[kTabMaxSlots];     // tiles summed of the row in a slot
   uint32_t drawn[kTabMaxSlots];    // draw items ended in a slot, over all its rows
   uint32_t ready[kTabMaxSlots];    // 1 + the row whose prefix a slot holds
-  uint32_t general[kTabMaxSlots];  // 1 + the row of a slot that is left to k_sample_redo
+  uint32_t kind[kTabMaxSlots];     // kTabKinds (1 + the last unusual row of a slot) + its kind
 };
 
 // Sets up the table with one exponential for every five entries: a magnitude is
 // (1 + h / 8 + l / 128) 2^x, so exp(z) is the entry at l = 0 times exp(+-l 2^(x
 // - 7)).  Ends with a barrier.
 __device__ __forceinline__ void tab_setup(TabLds& t) {
-  constexpr uint32_t T = kTabThreads, kHi = kTabSize / 16, kLo = kTabSize / 8;
+  constexpr uint32_t T = kTabThreads, kHi = kTabSize / 16, kLo = kTabBinades * 32;
+  if (threadIdx.x < 2) t.e[kTabSize + threadIdx.x] = 0.0;
   for (uint32_t j = threadIdx.x; j < kHi + kLo; j += T) {
     const bool high = j < kHi;
     // the high entries by (binade, h, sign), the low factors by (binade, l, sign)
@@ -855,18 +871,59 @@ __device__ __forceinline__ u16x2 tab_index(uint32_t x) {
   return __builtin_bit_cast(u16x2, t);
 }
 
-// exp(z) of any logit of a row that stays; `known` is cleared by a value that
-// no such row holds.  (By what the table holds, not by bounds of its own: a
-// value is in the table, below it, 0 in double, or unknown.)
-__device__ __forceinline__ double term_any(float z, const double* e, bool& known) {
-  const uint32_t b = __float_as_uint(z) >> 16;
-  const uint32_t t = (((b << 1) | (b >> 15)) - 2 * kTabBase) & 0xFFFFu;
-  if (t < kTabSize) return e[t];
-  const double d = (double)z;
-  // the next term of the series, z^4 / 24, is below 1.5e-22
-  if (fabsf(z) < kTabTiny) return fma(d, fma(d, fma(d, 1.0 / 6.0, 0.5), 1.0), 1.0);
-  known = known && z < kTabZero;
-  return 0.0;
+// The logit of a table offset, and the offset of -inf.
+__device__ __forceinline__ float tab_logit(uint32_t t) {
+  const uint32_t r = t + 2 * kTabBase;  // (16 bits of it)
+  return __uint_as_float(((r >> 1) & 0x7FFFu) << 16 | (r & 1u) << 31);
+}
+constexpr uint32_t kTabZeroAt = (2 * 0x7F80u + 1 - 2 * kTabBase) & 0xFFFFu;
+// The first offset of a logit below -820, and the first of a magnitude below
+// the table.
+constexpr uint32_t kTabZeroFrom = 2 * (0x444Du + 1 - kTabBase) + 1;
+constexpr uint32_t kTabTinyAt = 2 * (0x8000u - kTabBase);
+
+// What a row's values make of it; of several the last counts.
+enum TabKind : uint32_t { kTabUsual, kTabFarRow, kTabMarked, kTabUndef, kTabKinds };
+
+// Two offsets, those of the logits below -820 replaced by 0: the odd ones in
+// [kTabZeroFrom, kTabZeroAt].  (Packed 16-bit operations.)
+__device__ __forceinline__ u16x2 tab_rare(u16x2 t) {
+  constexpr uint16_t first = (uint16_t)kTabZeroFrom, n = (uint16_t)(kTabZeroAt + 1 - kTabZeroFrom);
+  const u16x2 in = __builtin_elementwise_sub_sat((u16x2)n, (u16x2)(t - first));  // 0: outside
+  const u16x2 odd = 0 - (t & (uint16_t)1);
+  return t & ~(odd & (0 - __builtin_elementwise_min(in, (u16x2)(uint16_t)1)));
+}
+
+// 1 where an offset is not a zero's.
+__device__ __forceinline__ u16x2 tab_not0(u16x2 t) {
+  return __builtin_elementwise_min((u16x2)((t ^ (uint16_t)kTabTinyAt) >> 1), (u16x2){1, 1});
+}
+
+// The term of such an offset past the near entries that the table does not hold
+// (0 otherwise), and the row's kind as far as is known.  (By what the table
+// holds, not by bounds of its own: a value is in the table, 0 in double, below
+// the table, or one that no row that stays holds.)
+__device__ __forceinline__ double tab_rare_term(uint32_t t, uint32_t& kind) {
+  double w = 0.0;
+  if (t >= kTabNear) {
+    const float z = tab_logit(t);
+    if (t >= kTabTinyAt) {
+      const double d = (double)z;
+      // the next term of the series, z^3 / 6, is below 7.5e-17
+      w = fma(d, fma(d, 0.5, 1.0), 1.0);
+    } else {
+      kind = max(kind, (uint32_t)(t < kTabSize ? kTabFarRow
+                                  : z < __builtin_huge_valf() ? kTabMarked : kTabUndef));
+    }
+  }
+  return w;
+}
+
+// The larger of a kind and a wave's (wave-uniform).
+__device__ __forceinline__ uint32_t tab_raise(uint32_t kind, uint32_t lane_kind) {
+  for (uint32_t k = kTabUndef; k > kind; --k)
+    if (__ballot(lane_kind == k) != 0) return k;
+  return kind;
 }
 
 struct TabTerms {
@@ -876,13 +933,15 @@ struct TabTerms {
   };
   __device__ __forceinline__ Chunk chunk(int64_t) const { return Chunk{1.0}; }
   __device__ __forceinline__ double operator()(float z, const Chunk&) const {
-    bool known = true;
-    return term_any(z, e, known);
+    const uint32_t b = __float_as_uint(z) >> 16;
+    const uint32_t t = (((b << 1) | (b >> 15)) - 2 * kTabBase) & 0xFFFFu;
+    uint32_t kind = kTabUsual;
+    return e[min(t, kTabSize)] + (t >= kTabTinyAt ? tab_rare_term(t, kind) : 0.0);
   }
 };
 
 // The terms of two vectors per lane, if the table holds those of the whole
-// wavefront (vectors outside the chunk read as -inf, which it does not).
+// wavefront or they are 0 (vectors outside the chunk read as -inf).
 __device__ __forceinline__ bool tab_terms(const InBf16::Vec (&x)[2], const double* e,
                                           double (&w)[8]) {
   u16x2 t[4], top = {0, 0};
@@ -891,7 +950,15 @@ __device__ __forceinline__ bool tab_terms(const InBf16::Vec (&x)[2], const doubl
     t[k] = tab_index(x[k / 2][k & 1]);
     top = __builtin_elementwise_max(top, t[k]);
   }
-  if (__ballot(top[0] >= kTabSize || top[1] >= kTabSize) != 0) return false;
+  if (__ballot(top[0] >= kTabSize || top[1] >= kTabSize) != 0) {
+    top = (u16x2){0, 0};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      top = __builtin_elementwise_max(top, tab_rare(t[k]));
+      t[k] = __builtin_elementwise_min(t[k], (u16x2)(uint16_t)kTabSize);
+    }
+    if (__ballot(top[0] >= kTabSize || top[1] >= kTabSize) != 0) return false;
+  }
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     w[2 * k] = e[t[k][0]];
@@ -923,6 +990,10 @@ __device__ __forceinline__ uint32_t lds_count(uint32_t* p) {
 __device__ __forceinline__ void lds_post(uint32_t* p, uint32_t v) {
   if ((threadIdx.x & 63) == 0)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_raise(uint32_t* p, uint32_t v) {
+  if ((threadIdx.x & 63) == 0)
+    __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 // (waits for a value, or for a count to reach one)
 __device__ __forceinline__ void lds_wait(const uint32_t* p, uint32_t v) {
@@ -982,10 +1053,25 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
       const double* s = sh.s + base;
       const double* p = sh.p + base;
       const double S = p[nchunk - 1];
-      if (lds_peek(&sh.general[slot]) == j + 1 || !(S >= kTabMinSum)) {
-        if (k == 0 && lane == 0) a.ids_out[row * M] = kSampleRedo;
+      const uint32_t seen = lds_peek(&sh.kind[slot]), own = kTabKinds * (j + 1);
+      const bool undef = seen == own + kTabUndef;
+      bool redo = !undef && (seen == own + kTabMarked || !(S >= kTabMinSum));
+      if (seen == own + kTabFarRow) {  // (every item of the row decides alike)
+        bool zero = false;
+        for (uint32_t i = lane; i < M; i += 64) zero |= a.u[row * M + i] == 0.f;
+        redo |= __ballot(zero) != 0;
+      }
+      if (redo || undef) {
+        if (redo && k == 0 && lane == 0) a.ids_out[row * M] = kSampleRedo;
         lds_release();
         lds_count(&sh.drawn[slot]);
+        if (undef) {
+          if (k == 0 && lane == 0 && a.lse_out) a.lse_out[row] = __builtin_nanf("");
+          if (mine) {
+            a.ids_out[row * M + m] = -1;
+            if (a.logp) a.logp[row * M + m] = __builtin_nanf("");
+          }
+        }
         return;
       }
       const double L = log(S);
@@ -1011,31 +1097,34 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
         step_load<TI>(zrow, c0, min(c0 + kSmpStepVecs, nvec), nvec, a.tail, x[d]);
       }
       const uint64_t oks = __ballot(ok);
+      uint32_t left = 0;
 #pragma unroll
       for (int d = 0; d < kTabDraws; ++d) {
         if (((oks >> d) & 1ull) == 0) continue;
-        const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)lo, d);
-        const uint32_t c0 = q * kSmpStepVecs, c1 = min(c0 + kSmpStepVecs, nvec);
-        const double rd = from_lane(r, d);
+        const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)lo, d) * kSmpStepVecs;
         double w[8], acc = 0.0;
-        if (!tab_terms(x[d], sh.e, w))
-          step_terms<TI>(x[d], c0, c1, TabTerms{sh.e}, TabTerms::Chunk{1.0}, w);
-        const int at = step_crossing(w, rd, 1.0, acc);
-        int64_t j_id = (int64_t)c0 * 4 + at;
-        if (at < 0) {
-          // rounding left no crossing: the chunk's last entry of mass, or that
-          // of the nearest chunk that has any
-          DrawAt da{(int64_t)q, rd, kLast};
-          if (!(s[q] > 0.0)) {
-            da.q = chunk_positive(s, q + 1, nchunk, false);
-            da.pick = kFirst;
-            if (da.q < 0) {
-              da.q = chunk_positive(s, 0, q, true);
-              da.pick = kLast;
-            }
+        int at = -1;
+        if (tab_terms(x[d], sh.e, w)) at = step_crossing(w, from_lane(r, d), 1.0, acc);
+        if (at < 0) left |= 1u << d;
+        else if (lane == d) id = (int32_t)(c0 * 4 + (uint32_t)at);
+      }
+      // chunks with unusual values, and those where rounding left no crossing: the
+      // chunk's last entry of mass then, or that of the nearest chunk that has any
+#pragma unroll 1
+      while (left != 0) {
+        const int d = __builtin_ctz(left);
+        left &= left - 1u;
+        DrawAt da{__builtin_amdgcn_readlane((int)lo, d), from_lane(r, d), kCross};
+        if (!(s[da.q] > 0.0)) {
+          const int64_t q = da.q;
+          da.q = chunk_positive(s, q + 1, nchunk, false);
+          da.pick = kFirst;
+          if (da.q < 0) {
+            da.q = chunk_positive(s, 0, q, true);
+            da.pick = kLast;
           }
-          j_id = smp_element<TI>(da, TabTerms{sh.e}, zrow, nvec, a.tail, kSmpStepVecs);
         }
+        const int64_t j_id = smp_element<TI>(da, TabTerms{sh.e}, zrow, nvec, a.tail, kSmpStepVecs);
         if (lane == d) id = (int32_t)j_id;
       }
       lp = mine && id >= 0 ? (float)((double)load_elem<TI>(zrow, id) - L) : __builtin_nanf("");
@@ -1081,45 +1170,64 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
     if (have) {
       const uint32_t j = tj, k = tk, t0 = k * TILE, slot = j % slots;
       double s0 = 0.0, s1 = 0.0;
-      bool known = true;
-      if (t0 + TILE <= nclean &&
-          __ballot(top[0] >= kTabSize || top[1] >= kTabSize) == 0) {  // wave-uniform
-        // (eight reads in flight: the scheduling barriers keep each batch whole)
+      uint32_t kind = kTabUsual;
+      if (t0 + TILE > nclean || __ballot(top[0] >= kTabNear || top[1] >= kTabNear) != 0) {
+        if (t0 + TILE > nclean) {  // (what is past the row's end reads as -inf)
+          const int left = (int)((uint32_t)a.V - 4u * (t0 + fresh_v(rowk * kSmpStepVecs + rl)));
 #pragma unroll
-        for (int h = 0; h < 2 * R; h += 4) {
-          double v[8];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            // offsets in bytes, both in 16 bits
-            const uint32_t o = __builtin_bit_cast(uint32_t, (u16x2)(t[h + i] << 3));
-            v[2 * i] = *(const double*)((const char*)sh.e + (o & 0xFFFFu));
-            v[2 * i + 1] = *(const double*)((const char*)sh.e + (o >> 16));
-          }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            s0 += v[2 * i];
-            s1 += v[2 * i + 1];
+          for (int i = 0; i < 2 * R; ++i) {
+            const int at = 64 * (i / 2) + 2 * (i & 1);
+            if (left <= at) t[i][0] = (uint16_t)kTabZeroAt;
+            if (left <= at + 1) t[i][1] = (uint16_t)kTabZeroAt;
           }
         }
-      } else {
-        // (from memory again: an index into x would put x there)
-        const char* zrow = row_ptr(row_of(j));
-#pragma unroll 1
-        for (int b = 0; b < R; ++b) {
-          const uint32_t v = t0 + rowk * kSmpStepVecs + rl + 16u * b;
-          if (v >= nvec) break;
-          float f[4];
-          unpack<TI>(load_vec<TI>(zrow, v, nvec, a.tail), f);
+        if (__ballot(top[0] >= kTabTinyAt || top[1] >= kTabTinyAt) != 0) {
+          // zeros: counted (their terms are 1), then as good as -inf
+          u16x2 n = {0, 0};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) s0 += term_any(f[e], sh.e, known);
+          for (int i = 0; i < 2 * R; ++i) {
+            const u16x2 not0 = tab_not0(t[i]), keep = 0 - not0;
+            n += not0;
+            t[i] = (t[i] & keep) | ((uint16_t)kTabZeroAt & ~keep);
+          }
+          n = (uint16_t)(2 * R) - n;
+          s0 = (double)(uint16_t)(n[0] + n[1]);
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * R; ++i) {
+          const u16x2 r = tab_rare(t[i]);
+          if (__ballot(r[0] >= kTabNear || r[1] >= kTabNear) != 0) {
+            uint32_t k2 = kTabUsual;
+            s0 += tab_rare_term(r[0], k2);
+            s1 += tab_rare_term(r[1], k2);
+            if (__ballot(k2 != kTabUsual) != 0) kind = tab_raise(kind, k2);
+          }
+          t[i] = __builtin_elementwise_min(t[i], (u16x2)(uint16_t)kTabSize);
+        }
+      }
+      // (eight reads in flight: the scheduling barriers keep each batch whole)
+#pragma unroll
+      for (int h = 0; h < 2 * R; h += 4) {
+        double v[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          // offsets in bytes, both in 16 bits
+          const uint32_t o = __builtin_bit_cast(uint32_t, (u16x2)(t[h + i] << 3));
+          v[2 * i] = *(const double*)((const char*)sh.e + (o & 0xFFFFu));
+          v[2 * i + 1] = *(const double*)((const char*)sh.e + (o >> 16));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s0 += v[2 * i];
+          s1 += v[2 * i + 1];
         }
       }
       const double sum = row16_sum(s0 + s1);
       // the slot's last row has been drawn from (see `draws`); until then its
       // mark and its records are still read
       lds_wait(&sh.drawn[slot], j / slots * ndraw);
-      if (__ballot(!known) != 0) lds_post(&sh.general[slot], j + 1);
+      if (kind != kTabUsual) lds_raise(&sh.kind[slot], kTabKinds * (j + 1) + kind);
       const uint32_t q = k * 4 + rowk;
       if (rl == 15 && q < nchunk) sh.s[slot * nchunk + q] = sum;
       lds_release();
@@ -1157,35 +1265,17 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
   }
 }
 
-// The rows that k_sample_tab left, one workgroup taking every gridDim.x-th; the
-// usual case, none, costs a short grid that reads the marks.
-constexpr int kSampleRedoGroups = 512;
+// The rows that k_sample_tab left, a workgroup each, five to a CU as in k_sample;
+// the usual case, none, costs a grid of workgroups that read a mark and end.
+// (One workgroup taking several rows would hold 161 registers, three to a CU.)
 __global__ void __launch_bounds__(kSmpThreads) k_sample_redo(CacheArgs a) {
   __shared__ SmpLds<kSmpThreads, kSmpMaxChunks> c;
-  __shared__ uint32_t s_n;
-  __shared__ int64_t s_rows[kSmpThreads];
-  constexpr int T = kSmpThreads;
-  const int64_t stride = (int64_t)gridDim.x;
-  bool tab = false;
-  for (int64_t base = blockIdx.x; base < a.N; base += stride * T) {  // workgroup-uniform
-    if (threadIdx.x == 0) s_n = 0u;
-    __syncthreads();
-    const int64_t row = base + (int64_t)threadIdx.x * stride;
-    if (row < a.N && (!a.mask || a.mask[row] != 0) && a.ids_out[row * a.K] == kSampleRedo)
-      s_rows[atomicAdd(&s_n, 1u)] = row;
-    __syncthreads();
-    const uint32_t n = s_n;
-    if (n != 0 && !tab) {
-      for (int j = threadIdx.x; j < kExpTab; j += T) c.tab[j] = exp2((double)j / kExpTab);
-      tab = true;
-      __syncthreads();
-    }
-    for (uint32_t i = 0; i < n; ++i) {
-      sample_row<InBf16, false>(a, s_rows[i],
-                                (const char*)a.logits + s_rows[i] * a.ld * InBf16::BYTES, c);
-      __syncthreads();  // the next row's records wait for this row's draws
-    }
-  }
+  const int64_t row = xcd_remap(blockIdx.x, gridDim.x);
+  if ((a.mask && a.mask[row] == 0) || a.ids_out[row * a.K] != kSampleRedo) return;
+  // (every lane has read the mark before one overwrites it: sample_row has barriers)
+  for (int j = threadIdx.x; j < kExpTab; j += kSmpThreads) c.tab[j] = exp2((double)j / kExpTab);
+  __syncthreads();
+  sample_row<InBf16, false>(a, row, (const char*)a.logits + row * a.ld * InBf16::BYTES, c);
 }
 
 // ---------------------------------------------------------------- top-k
@@ -1965,8 +2055,7 @@ hipError_t launch_dt(const CacheArgs& a, CacheOp op, bool resident, hipStream_t 
                            dim3(kTabThreads), 0, stream, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_sample_redo, dim3((unsigned)min(a.N, (int64_t)kSampleRedoGroups)),
-                           dim3(kSmpThreads), 0, stream, a);
+        hipLaunchKernelGGL(k_sample_redo, dim3((unsigned)a.N), dim3(kSmpThreads), 0, stream, a);
         return hipGetLastError();
       }
     }

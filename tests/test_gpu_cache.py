@@ -296,6 +296,56 @@ def test_sample_logits_at_the_tables_lower_edge(edge):
                 synth.BF16, u, ref)
 
 
+@pytest.mark.parametrize("zero", [False, True])
+@pytest.mark.parametrize("edge", [350.0, 352.0, 636.0, 640.0, 700.0, 2.0 ** -17, 2.0 ** -18,
+                                  -350.0, -352.0, -636.0, -640.0, -820.0, -824.0, -1e30])
+def test_sample_values_at_the_tables_edges(edge, zero):
+    """Each end of the ranges that the table kernel tells apart: as one entry of
+    an ordinary row, as a row's first entry, as every entry, beside its
+    opposite, and in every other entry; at uniforms of 0, where an entry that
+    underflows beside the row's maximum must not be drawn, and without."""
+    V, N, M = 16385, 6, 16
+    rng = np.random.default_rng(9)
+    x = rng.normal(0.0, 3.0, (N, V)).astype(np.float32)
+    x[0, V - 1] = edge
+    x[1, 0] = edge
+    x[2] = max(edge, -1e6)  # (below, log V is lost beside the entry in the oracle's CDF)
+    x[3, 0], x[3, 5000] = -abs(edge), abs(edge)
+    x[4, ::2] = edge
+    x[5, :4096] = -abs(edge)
+    ld = 16392
+    stored = np.zeros((N, ld), np.uint16)
+    stored[:, :V] = to_stored(x, synth.BF16)
+    say("sample table edge %g zero=%d" % (edge, zero))
+    u = f32_uniforms(78, N, M)
+    u[:, 1] = np.nextafter(np.float32(1), np.float32(0))
+    if zero:
+        u[:, 3] = 0.0
+    out = opd.sample_actions(as_device(stored, V), to_dev(u), want_lse=True)
+    torch.cuda.synchronize()
+    ref = oracle.cache_rows("sample", synth.BF16, stored, V, M, uniforms=u)
+    lse = out["lse"].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(lse - ref["lse"]) <= LP_TOL * (1 + np.abs(ref["lse"])))
+    check_draws("edge", out["ids"].cpu().numpy(), out["logp"].cpu().numpy(), stored, V,
+                synth.BF16, u, ref)
+
+
+def test_sample_undefined_rows_of_the_table_kernel():
+    """A NaN or +inf anywhere in a row, beside values of every other kind."""
+    V, N, M = 20000, 12, 9
+    x = np.random.default_rng(10).normal(0.0, 3.0, (N, V)).astype(np.float32)
+    for r in range(0, N, 2):
+        x[r, (0, V - 1, 12345)[r // 2 % 3]] = (np.nan, np.inf)[r // 6]
+    x[0, 7], x[4, 9], x[6, 11], x[8, 5] = 700.0, 400.0, -700.0, -np.inf
+    say("sample undefined rows")
+    u = f32_uniforms(79, N, M)
+    out = opd.sample_actions(as_device(to_stored(x, synth.BF16), V), to_dev(u), want_lse=True)
+    torch.cuda.synchronize()
+    ids, logp, lse = (out[k].cpu().numpy() for k in ("ids", "logp", "lse"))
+    assert np.all(ids[::2] == -1) and np.isnan(logp[::2]).all() and np.isnan(lse[::2]).all()
+    assert np.all(ids[1::2] >= 0) and np.isfinite(logp[1::2]).all() and np.isfinite(lse[1::2]).all()
+
+
 @pytest.mark.parametrize("V,N,M,check", [
     (655360, 256 * 3 + 7, 16, 97),   # two slots: each is used again by the row after next
     (16390, 256 * 10 + 3, 9, None),  # eight slots, and a short last tile
@@ -311,10 +361,10 @@ def test_sample_table_slots_are_used_again_by_marked_rows(V, N, M, check):
     rng = np.random.default_rng(V)
     kinds = 8
     base = rng.normal(0.0, 3.0, (kinds, V)).astype(np.float32)
-    for i, (at, z) in enumerate([(3, 400.0), (V - 1, -500.0), (V - 2, np.inf), (5, np.nan),
-                                 (V - 1, 400.0), (7, -500.0), (V - 3, np.nan)]):
+    for i, (at, z) in enumerate([(3, 704.0), (V - 1, -700.0), (V - 2, np.inf), (5, np.nan),
+                                 (V - 1, 704.0), (7, -700.0), (V - 3, np.nan)]):
         base[i, at] = z
-    base[0, V // 2] = 399.0
+    base[0, V // 2] = 703.0  # (704 in bf16)
     kind = np.where(np.arange(N) // 256 % 5 == 4, 7, rng.integers(0, 7, N))
     rows = np.zeros((kinds, ld), np.uint16)
     rows[:, :V] = to_stored(base, synth.BF16)
