@@ -797,7 +797,6 @@ constexpr int kTabThreads = 1024;
 constexpr int kTabRing = 2560;                  // records in the ring
 constexpr int kTabMaxSlots = 8;
 constexpr int kTabMaxChunks = kTabRing / 2;     // rows up to 655,360 entries
-constexpr int64_t kTabMinVec = 4096;
 constexpr int kTabCus = 256;
 constexpr int kTabDraws = 4;                    // draws per item
 constexpr uint32_t kTabLoExp = 110;             // biased exponent of 2^-17
@@ -2046,11 +2045,25 @@ hipError_t launch_op(const CacheArgs& a, CacheOp op, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Whether bf16 rows are drawn from the table.  Setting it up, and the draws of an
+// item one after the other, cost what k_sample's double-precision terms cost on
+// few narrow rows with few draws.  Measured, table against k_sample: 64 rows of V =
+// 16,384, M = 1 12.1 / 10.2 us, M = 4 1.32 times, M = 8 1.07 times; 24,576 M = 1 1.01, M = 4
+// 1.09; 32,000 M = 4 1.04 times; 512 rows of 22,000 M = 1 1.07, M = 4 1.12 times, of 24,576
+// 0.91 and 1.02; 1,024 rows of 16,384 (eight whole tiles) M = 1 0.92, of 18,000 1.06, of
+// 20,000 0.99; 16 draws 0.97 and less everywhere.
+bool draws_from_table(const CacheArgs& a) {
+  if (a.nvec < 4096 || a.nvec > (int64_t)kTabMaxChunks * kSmpStepVecs) return false;
+  if (a.N <= 256) return a.K > 8 || a.nvec >= (a.K > 4 ? 5600 : 5600 + 1100 * a.K);
+  if (a.K > 4 || a.N > 1024) return true;
+  return a.N <= 640 ? a.nvec >= 5800 : a.nvec == 4096 || a.nvec >= 5000;
+}
+
 template <class TI>
 hipError_t launch_dt(const CacheArgs& a, CacheOp op, bool resident, hipStream_t stream) {
   if (op == CacheOp::Sample) {
     if constexpr (TI::BYTES == 2) {
-      if (a.nvec >= kTabMinVec && a.nvec <= (int64_t)kTabMaxChunks * kSmpStepVecs) {
+      if (draws_from_table(a)) {
         hipLaunchKernelGGL(k_sample_tab, dim3((unsigned)min(a.N, (int64_t)kTabCus)),
                            dim3(kTabThreads), 0, stream, a);
         const hipError_t e = hipGetLastError();

@@ -267,6 +267,24 @@ def test_sample_table_rows(V, ld, N, M):
     assert np.all(np.abs(lse - ref["lse"])[defined] <= LP_TOL * (1 + np.abs(ref["lse"][defined])))
 
 
+@pytest.mark.parametrize("V,N,M", [
+    (16376, 700, 9), (16384, 641, 1), (16384, 640, 1), (16384, 257, 5), (16384, 3, 9),
+    (16384, 3, 8), (22392, 3, 8), (22400, 3, 8), (26792, 256, 1), (26800, 256, 1),
+    (39992, 3, 4), (40000, 3, 4), (23192, 300, 4), (23200, 300, 4), (16392, 641, 4),
+    (19992, 1024, 4), (16392, 1025, 4)])
+def test_sample_both_sides_of_the_tables_rule(V, N, M):
+    """Widths, row counts and draws on both sides of each line between the table
+    kernel and the general one."""
+    say("sample rule V=%d N=%d M=%d" % (V, N, M))
+    stored = make_logits(V, V, synth.BF16, N)
+    u = f32_uniforms(V + N + M, N, M)
+    out = opd.sample_actions(as_device(stored, V), to_dev(u), want_lse=True)
+    torch.cuda.synchronize()
+    ref = oracle.cache_rows("sample", synth.BF16, stored, V, M, uniforms=u)
+    check_draws("rule", out["ids"].cpu().numpy(), out["logp"].cpu().numpy(), stored, V,
+                synth.BF16, u, ref)
+
+
 @pytest.mark.parametrize("edge", [-64.0, -63.75, -64.5])
 def test_sample_logits_at_the_tables_lower_edge(edge):
     """Logits at and beside -64, the lower edge of the table kernel's values,
