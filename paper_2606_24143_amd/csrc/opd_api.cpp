@@ -256,8 +256,9 @@ bool row_fits(int64_t nvec, int32_t dtype) {
 
 // Workspace of opd_mc_diagnostics: regions in order, each 256-byte aligned.
 struct DiagLayout {
-  size_t rho, x, psum, parts, hist, total;
+  size_t rho, x, psum, seq, parts, hist, total;
   int64_t nseq, pieces;
+  int seq_groups;
 };
 
 DiagLayout diag_layout(int64_t N, int32_t M, int32_t n_groups, int64_t seq_len) {
@@ -272,7 +273,9 @@ DiagLayout diag_layout(int64_t N, int32_t M, int32_t n_groups, int64_t seq_len) 
   l.pieces = seq ? opd::diag_pieces(N, seq_len) : 0;
   l.rho = take((size_t)N * M * 4);
   l.x = seq ? take((size_t)N * M * 4) : 0;
-  l.psum = seq ? take((size_t)(l.nseq * l.pieces) * (M + 1) * 8) : 0;
+  l.psum = l.pieces > 0 ? take((size_t)(l.nseq * l.pieces) * (M + 1) * 8) : 0;
+  l.seq_groups = seq ? opd::diag_seq_groups(l.nseq, M, n_groups) : 0;
+  l.seq = seq ? take((size_t)l.seq_groups * (opd::kDiagMaxGroups + 1) * 8) : 0;
   l.parts = take((size_t)opd::diag_parts(N) * (3 + opd::kDiagMaxGroups) * 8);
   l.hist = take((size_t)opd::kDiagHistWords * 4);
   return l;
@@ -566,7 +569,10 @@ int opd_mc_diagnostics(const float* lse, const float* gathered, const float* tea
   char* ws = (char*)workspace;
   a.ws_rho = (uint32_t*)(ws + l.rho);
   a.ws_x = l.nseq && out->ratio_seq ? (float*)(ws + l.x) : nullptr;
-  a.ws_psum = a.ws_x ? (double*)(ws + l.psum) : nullptr;
+  a.ws_psum = a.ws_x && l.pieces > 0 ? (double*)(ws + l.psum) : nullptr;
+  a.ws_seq = a.ws_x ? (double*)(ws + l.seq) : nullptr;
+  a.seq_groups = l.seq_groups;
+  a.seq_batch = opd::diag_seq_batch(M, n_groups);
   a.ws_parts = (double*)(ws + l.parts);
   a.ws_hist = (uint32_t*)(ws + l.hist);
   const hipError_t err = opd::launch_diag(a, (hipStream_t)stream);

@@ -17,9 +17,12 @@
 //   mid      the histogram of the next 11 bits within the bucket that holds the
 //            wanted rank; and, in workgroups of their own, sums of the X
 //            columns over pieces of the sequences
-//   low      the histogram of the last 10 bits
-//   final    the quantile; fixed-order sums of the parts in double; the
-//            per-sequence set variances; the batch outputs
+//   low      the histogram of the last 10 bits; and, in up to kDiagSeqGroups
+//            workgroups of their own, the column averages of each sequence (from
+//            the pieces, or from X where a sequence is short), the set variances
+//            and their sums
+//   final    the quantile; fixed-order sums of the parts in double; the batch
+//            outputs
 // rho >= 0, so its bits order like values.  Integer histograms make the
 // selection exact and order-independent; every floating-point sum has a fixed
 // order.  Measured (32,768 tokens, M = 16, three group sizes, 2,048-token
@@ -281,9 +284,93 @@ __device__ __forceinline__ Picked Pick<T, PASS>::find(const DiagArgs& a, uint32_
   return r;
 }
 
+// Sequence level: set 0 = the M single-draw columns, set k >= 1 = the means of
+// group[k - 1] consecutive ones (a column's average over tokens commutes with the
+// mean over draws); sequences without a valid token are skipped.  Workgroup b
+// takes a range of sequences, as many at a time as fill its lanes, and leaves each
+// set's sum of variances over them, in order.
+__device__ __forceinline__ void seq_variances(const DiagArgs& a, int b, double* s_avg,
+                                              double* s_var) {
+  constexpr int T = kDiagThreads;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int M = a.M, sets = a.n_groups + 1;
+  static_assert(T == kDiagSeqLanes, "a lane for each column and each set of a batch");
+  const int64_t batch = a.seq_batch;
+  // whole batches to a workgroup
+  const int64_t per = ((a.nseq + batch - 1) / batch + a.seq_groups - 1) / a.seq_groups * batch;
+  const int64_t s_end = min((int64_t)(b + 1) * per, a.nseq);
+  double seq = 0.0;  // lane k < sets: set k
+  for (int64_t s0 = (int64_t)b * per; s0 < s_end; s0 += batch) {
+    const int ns = (int)min(batch, s_end - s0);
+    if (tid < ns * M) {  // a column's average over the valid tokens of one sequence
+      const int64_t s = s0 + tid / M;
+      const int c = tid % M;
+      double v = 0.0, n = 0.0;
+      if (a.ws_psum) {
+        const double* p = a.ws_psum + s * a.pieces * (M + 1);
+#pragma unroll 8
+        for (int64_t k = 0; k < a.pieces; ++k) {
+          v += p[k * (M + 1) + c];
+          n += p[k * (M + 1) + M];
+        }
+      } else {
+        const int64_t t0 = s * a.seq_len, t1 = min(t0 + a.seq_len, a.N);
+#pragma unroll 8
+        for (int64_t t = t0; t < t1; ++t) {  // (a masked token's terms are 0)
+          v += (double)a.ws_x[t * M + c];
+          n += !a.mask || a.mask[t] != 0 ? 1.0 : 0.0;
+        }
+      }
+      s_avg[tid] = n > 0.0 ? v / n : __builtin_nan("");
+    }
+    __syncthreads();
+    if (M <= 64) {
+      // a lane for each set of each sequence
+      if (tid < ns * sets) {
+        const int k = tid % sets, m = k ? a.group[k - 1] : 1, n = M / m;
+        const double* avg = s_avg + (tid / sets) * M;
+        double mean = 0.0;
+        for (int c = 0; c < n * m; ++c) mean += avg[c];
+        mean /= (double)(n * m);
+        double ss = 0.0;
+        for (int g = 0; g < n; ++g) {
+          double y = 0.0;
+          for (int c = g * m; c < g * m + m; ++c) y += avg[c];
+          y = y / m - mean;
+          ss += y * y;
+        }
+        s_var[tid] = avg[0] == avg[0] ? ss / (n - 1) : 0.0;
+      }
+    } else {
+      // a wave for each, its lanes over the columns and then the groups
+      for (int i = w; i < ns * sets; i += T / 64) {
+        const int k = i % sets, m = k ? a.group[k - 1] : 1, n = M / m;
+        const double* avg = s_avg + (i / sets) * M;
+        double v = 0.0;
+        for (int c = lane; c < n * m; c += 64) v += avg[c];
+        const double mean = __shfl(wave_sum_f64(v), 63, 64) / (double)(n * m);
+        double ss = 0.0;
+        for (int g = lane; g < n; g += 64) {
+          double y = 0.0;
+          for (int c = g * m; c < g * m + m; ++c) y += avg[c];
+          y = y / m - mean;
+          ss += y * y;
+        }
+        ss = wave_sum_f64(ss);
+        if (lane == 63) s_var[i] = avg[0] == avg[0] ? ss / (n - 1) : 0.0;
+      }
+    }
+    __syncthreads();
+    if (tid < sets)
+      for (int s = 0; s < ns; ++s) seq += s_var[s * sets + tid];
+    __syncthreads();
+  }
+  if (tid < sets) a.ws_seq[(int64_t)b * (kDiagMaxGroups + 1) + tid] = seq;
+}
+
 // The histogram of one of the later digits, over the keys whose earlier ones
-// are the picked bucket's; in pass 1, workgroups from hist_groups on sum one
-// piece of a sequence each.
+// are the picked bucket's; workgroups from hist_groups on sum one piece of a
+// sequence each in pass 1, and make the set variances in pass 2.
 template <int PASS>
 __global__ void __launch_bounds__(kDiagThreads) k_diag_hist(DiagArgs a, unsigned hist_groups) {
   __shared__ uint32_t h[digit_bins(PASS)];
@@ -321,6 +408,12 @@ __global__ void __launch_bounds__(kDiagThreads) k_diag_hist(DiagArgs a, unsigned
     }
     return;
   }
+  if (PASS == 2 && blockIdx.x >= hist_groups) {
+    __shared__ double s_avg[kDiagThreads];
+    __shared__ double s_var[kDiagThreads];
+    seq_variances(a, (int)(blockIdx.x - hist_groups), s_avg, s_var);
+    return;
+  }
   Pick<kDiagThreads, PASS - 1> before;
   before.load(a);
   const Picked p = before.find(a, PASS == 1 ? 0u : a.ws_hist[kSel],
@@ -352,15 +445,13 @@ __global__ void __launch_bounds__(kDiagThreads) k_diag_hist(DiagArgs a, unsigned
 
 // One workgroup: the quantile, the batch sums, the sequence-level ratios.
 constexpr int kFinalThreads = 1024;
-constexpr int kFinalAvg = 2048;  // column averages of a batch of sequences
 
 __global__ void __launch_bounds__(kFinalThreads) k_diag_final(DiagArgs a, int parts) {
   constexpr int T = kFinalThreads, W = T / 64;
   __shared__ uint32_t s_w[W], s_out[2];
-  __shared__ double s_avg[kFinalAvg];
-  __shared__ double s_var[kFinalAvg];
   static_assert(kDiagQ <= W, "a wave for each quantity");
   __shared__ double tot[kDiagQ];
+  __shared__ double seq[kDiagMaxGroups + 1];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int M = a.M, sets = a.n_groups + 1;
   // what every part below needs from memory is requested first: one round trip
@@ -371,28 +462,23 @@ __global__ void __launch_bounds__(kFinalThreads) k_diag_final(DiagArgs a, int pa
     prefix = a.ws_hist[kSel + 2];
     rank = a.ws_hist[kSel + 3];
   }
-  // a column's average over the valid tokens of one sequence
-  auto average = [&](int64_t s, int c) {
-    const double* p = a.ws_psum + s * a.pieces * (M + 1);
-    double v = 0.0, n = 0.0;
-#pragma unroll 8
-    for (int64_t k = 0; k < a.pieces; ++k) {
-      v += p[k * (M + 1) + c];
-      n += p[k * (M + 1) + M];
-    }
-    return n > 0.0 ? v / n : __builtin_nan("");
-  };
-  const bool with_seq = a.ratio_seq && a.ws_psum;
-  const int64_t batch = kFinalAvg / (M > sets ? M : sets);
-  double avg0 = 0.0;  // this lane's column of the first batch
-  if (with_seq && tid < (int)min(batch, a.nseq) * M) avg0 = average(tid / M, tid % M);
-  // batch sums: wave i adds the parts of quantity i
+  const bool with_seq = a.ratio_seq && a.ws_seq;
+  // batch sums: wave i adds the parts of quantity i, and those of set i
+  double v = 0.0, sv = 0.0;
   if (w < 3 + a.n_groups) {
-    double v = 0.0;
 #pragma unroll 8
     for (int p = lane; p < parts; p += 64) v += a.ws_parts[(int64_t)p * kDiagQ + w];
-    v = wave_sum_f64(v);
-    if (lane == 63) tot[w] = v;
+  }
+  if (with_seq && w < sets) {
+#pragma unroll 4
+    for (int p = lane; p < a.seq_groups; p += 64)
+      sv += a.ws_seq[(int64_t)p * (kDiagMaxGroups + 1) + w];
+  }
+  v = wave_sum_f64(v);
+  sv = wave_sum_f64(sv);
+  if (lane == 63) {
+    if (w < 3 + a.n_groups) tot[w] = v;
+    if (w < sets) seq[w] = sv;
   }
   __syncthreads();
   if (a.rho_quantile) {
@@ -400,46 +486,12 @@ __global__ void __launch_bounds__(kFinalThreads) k_diag_final(DiagArgs a, int pa
     // (tot[2] valid tokens; none: no ratio)
     if (tid == 0) a.rho_quantile[0] = tot[2] > 0.0 ? __uint_as_float(p.prefix) : __builtin_nanf("");
   }
-  // sequence level: set 0 = the M single-draw columns, set k >= 1 = the means
-  // of group[k - 1] consecutive ones (a column's average over tokens commutes
-  // with the mean over draws); sequences without a valid token are skipped.
-  // Lane k < sets keeps set k's sum over the sequences, in order.
-  double seq = 0.0;
-  if (with_seq) {
-    for (int64_t s0 = 0; s0 < a.nseq; s0 += batch) {
-      const int ns = (int)min(batch, a.nseq - s0);
-      for (int i = tid; i < ns * M; i += T)
-        s_avg[i] = s0 == 0 && i == tid ? avg0 : average(s0 + i / M, i % M);
-      __syncthreads();
-      for (int i = tid; i < ns * sets; i += T) {
-        const int k = i % sets, m = k ? a.group[k - 1] : 1, n = M / m;
-        const double* avg = s_avg + (i / sets) * M;
-        double mean = 0.0;
-        for (int c = 0; c < n * m; ++c) mean += avg[c];
-        mean /= (double)(n * m);
-        double ss = 0.0;
-        for (int g = 0; g < n; ++g) {
-          double y = 0.0;
-          for (int c = g * m; c < g * m + m; ++c) y += avg[c];
-          y = y / m - mean;
-          ss += y * y;
-        }
-        s_var[i] = avg[0] == avg[0] ? ss / (n - 1) : 0.0;
-      }
-      __syncthreads();
-      if (tid < sets)
-        for (int s = 0; s < ns; ++s) seq += s_var[s * sets + tid];
-      __syncthreads();
-    }
-    if (tid < sets) s_avg[tid] = seq;
-    __syncthreads();
-  }
   if (tid == 0) {
     const double n = tot[2] * (double)M;
     if (a.clip_frac) a.clip_frac[0] = n > 0 ? (float)(tot[1] / n) : __builtin_nanf("");
     for (int k = 0; k < a.n_groups; ++k) {
       if (a.ratio_local) a.ratio_local[k] = (float)(tot[3 + k] / tot[0]);
-      if (with_seq) a.ratio_seq[k] = (float)(s_avg[1 + k] / s_avg[0]);
+      if (with_seq) a.ratio_seq[k] = (float)(seq[1 + k] / seq[0]);
     }
   }
 }
@@ -467,9 +519,11 @@ hipError_t launch_diag(const DiagArgs& a, hipStream_t stream) {
   const int64_t quads = (a.N * a.M / 4 + kDiagThreads - 1) / kDiagThreads;
   const unsigned groups = a.rho_quantile ? (unsigned)(quads < 1 ? 1 : (quads < 512 ? quads : 512)) : 0u;
   const unsigned pieces = a.ws_psum ? (unsigned)(a.nseq * a.pieces) : 0u;
+  const unsigned seqs = a.ws_seq ? (unsigned)a.seq_groups : 0u;
   if (groups + pieces > 0)
     hipLaunchKernelGGL(k_diag_hist<1>, dim3(groups + pieces), blk, 0, stream, a, groups);
-  if (a.rho_quantile) hipLaunchKernelGGL(k_diag_hist<2>, dim3(groups), blk, 0, stream, a, groups);
+  if (groups + seqs > 0)
+    hipLaunchKernelGGL(k_diag_hist<2>, dim3(groups + seqs), blk, 0, stream, a, groups);
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kFinalThreads), 0, stream, a, parts);
   return hipGetLastError();
 }

@@ -102,10 +102,26 @@ inline int diag_parts(int64_t N) {
 }
 // quantile histograms of 10, 11 and 10 bits, and four words of state
 constexpr int kDiagHistWords = 1024 + 2048 + 1024 + 4;
-// pieces that a sequence's columns are summed in, a workgroup each
-constexpr int64_t kDiagPiece = 128;  // tokens
+// pieces that a sequence's columns are summed in, a workgroup each (0: a sequence
+// of few tokens, summed where its variances are made; measured, 2,048 tokens of 16
+// draws: sequences of 128 tokens 30.2 us so and 23.3 with pieces, of 32 25.2 so, of 33
+// 23.7 with pieces, of 1 23.7 so, which would take a workgroup for each token)
+constexpr int64_t kDiagPiece = 128, kDiagShortSeq = 32;  // tokens
 inline int64_t diag_pieces(int64_t N, int64_t seq_len) {
+  if (seq_len <= kDiagShortSeq) return 0;
   return ((seq_len < N ? seq_len : N) + kDiagPiece - 1) / kDiagPiece;
+}
+// workgroups that make the sequences' set variances at most; each takes
+// sequences in batches that fill its lanes (one for each column, and for each
+// set)
+constexpr int64_t kDiagSeqGroups = 512;
+constexpr int kDiagSeqLanes = 256;
+inline int diag_seq_batch(int M, int n_groups) {
+  return kDiagSeqLanes / (M > n_groups + 1 ? M : n_groups + 1);
+}
+inline int diag_seq_groups(int64_t nseq, int M, int n_groups) {
+  const int64_t batch = diag_seq_batch(M, n_groups), g = (nseq + batch - 1) / batch;
+  return (int)(g < kDiagSeqGroups ? g : kDiagSeqGroups);
 }
 
 struct DiagArgs {
@@ -121,12 +137,15 @@ struct DiagArgs {
   int group[kDiagMaxGroups];
   int64_t seq_len, nseq;
   int64_t pieces;         // of a sequence (diag_pieces)
+  int seq_groups, seq_batch;  // diag_seq_groups, diag_seq_batch (sequence ratios only)
   // outputs (nullable)
   float *row_mean, *row_var, *row_rho_max, *rho_quantile, *clip_frac, *ratio_local, *ratio_seq;
   // workspace
   uint32_t* ws_rho;       // [N, M] sort keys of the ratios
   float* ws_x;            // [N, M] one-sample terms (sequence ratios only, else NULL)
-  double* ws_psum;        // [nseq, pieces, M + 1] column sums and valid tokens (the same)
+  double* ws_psum;        // [nseq, pieces, M + 1] column sums and valid tokens of the
+                          // pieces (as ws_x; NULL without)
+  double* ws_seq;         // [seq_groups, kDiagMaxGroups + 1] sums of set variances (as ws_x)
   double* ws_parts;       // [diag_parts, 3 + kDiagMaxGroups] first-stage sums
   uint32_t* ws_hist;      // [kDiagHistWords] radix-select histograms and state
 };

@@ -98,6 +98,14 @@ def test_diag_parity(N, M, groups, seq, ragged, q):
     (1100, 33, (3, 11), 257),    # odd sizes, a short last sequence
     (520, 64, (2, 32), 128),     # the most draws with one entry to a lane
     (300, 100, (1, 2, 4, 5, 10, 20, 25, 50), 300),  # the most group sizes
+    (20000, 16, (2, 4, 8), 1),    # more sequences than one batch of every workgroup
+    (9001, 2, (1,), 1),
+    (700, 256, (1, 2, 128), 1),   # a sequence at a time, a wave for each set
+    (3000, 65, (1, 5, 13), 7),
+    (5000, 64, (1, 32), 32),      # the longest sequence summed without a piece
+    (5000, 64, (1, 32), 33),      # and the shortest with one
+    (513, 2, (1,), 128),          # one whole piece
+    (1290, 4, (1, 2), 129),
 ])
 def test_diag_sizes(N, M, groups, seq):
     """Lanes per token, pieces of sequences and parts of the batch at their
