@@ -300,19 +300,19 @@ int opd_validate_cache(const opd_cache* cache, int32_t estimator, int64_t N, int
  * p_old for Stage 1, the teacher for Stage 2) with the same dtype, ld and
  * alignment rules as opd_loss_fwd_bwd, and writes per-row results.  A masked
  * row (mask[t] == 0) is not read and gets 0 in every output.  lse_out, when
- * not NULL, receives log sum_j exp(z_j) per row.  No workspace; one
- * workgroup per row.
+ * not NULL, receives log sum_j exp(z_j) per row.  No workspace.
  *
  * opd_sample_actions: M iid draws per row from softmax(z), as the rollout
  *   makes them (temperature 1, no top-p or top-k truncation; App. B), by
  *   inversion: draw i is the first index whose cumulative probability (index
  *   order) exceeds uniforms[t, i].  The uniforms are supplied by the caller
  *   ([N, M] fp32 in [0, 1)), so the draws are a deterministic function of
- *   them.  The CDF is evaluated in double precision (terms exp(z_j - max) to
- *   about 1.5e-15 relative, double sums), so a draw is the one exact arithmetic
- *   gives unless uniforms[t, i] lies within about 1e-14 of a cumulative value;
- *   terms follow double's gradual underflow, -inf logits have exactly zero
- *   mass, and a drawn id always has nonzero probability.
+ *   them.  The CDF is evaluated in double precision (terms exp(z_j - max), or
+ *   terms in proportion to them, to about 1.5e-15 relative, double sums), so a
+ *   draw is the one exact arithmetic gives unless uniforms[t, i] lies within
+ *   about 1e-14 of a cumulative value; terms follow double's gradual underflow
+ *   below the row's maximum, -inf logits have exactly zero mass, and a drawn id
+ *   always has nonzero probability.
  *     sampled_ids [N, M] int32 out; logp [N, M] fp32 out (nullable) =
  *     log softmax(z) at the draw, the rollout-time log-probability the MC
  *     estimators read as behav_logp.  A uniform outside [0, 1) (or NaN), or a

@@ -884,19 +884,21 @@ constexpr uint32_t kTabTinyAt = 2 * (0x8000u - kTabBase);
 // What a row's values make of it; of several the last counts.
 enum TabKind : uint32_t { kTabUsual, kTabFarRow, kTabMarked, kTabUndef, kTabKinds };
 
+// A pair of 16-bit constants, made where it is used: held in scalar registers
+// across the kernel's loop they would push others out.
+__device__ __forceinline__ u16x2 pair_of(uint32_t x) {
+  return __builtin_bit_cast(u16x2, fresh_s(x * 0x10001u));
+}
 // Two offsets, those of the logits below -820 replaced by 0: the odd ones in
 // [kTabZeroFrom, kTabZeroAt].  (Packed 16-bit operations.)
-__device__ __forceinline__ u16x2 tab_rare(u16x2 t) {
-  constexpr uint16_t first = (uint16_t)kTabZeroFrom, n = (uint16_t)(kTabZeroAt + 1 - kTabZeroFrom);
-  const u16x2 in = __builtin_elementwise_sub_sat((u16x2)n, (u16x2)(t - first));  // 0: outside
-  const u16x2 odd = 0 - (t & (uint16_t)1);
-  return t & ~(odd & (0 - __builtin_elementwise_min(in, (u16x2)(uint16_t)1)));
-}
-
-// 1 where an offset is not a zero's.
-__device__ __forceinline__ u16x2 tab_not0(u16x2 t) {
-  return __builtin_elementwise_min((u16x2)((t ^ (uint16_t)kTabTinyAt) >> 1), (u16x2){1, 1});
-}
+struct TabRare {
+  u16x2 first = pair_of(kTabZeroFrom), n = pair_of(kTabZeroAt + 1 - kTabZeroFrom), one = pair_of(1);
+  __device__ __forceinline__ u16x2 operator()(u16x2 t) const {
+    const u16x2 past = __builtin_elementwise_sub_sat(n, (u16x2)(t - first));  // 0: outside
+    const u16x2 zero = t & __builtin_elementwise_min(past, one);  // 1: odd, inside
+    return t & (zero - one);
+  }
+};
 
 // The term of such an offset past the near entries that the table does not hold
 // (0 otherwise), and the row's kind as far as is known.  (By what the table
@@ -950,11 +952,13 @@ __device__ __forceinline__ bool tab_terms(const InBf16::Vec (&x)[2], const doubl
     top = __builtin_elementwise_max(top, t[k]);
   }
   if (__ballot(top[0] >= kTabSize || top[1] >= kTabSize) != 0) {
+    const TabRare rare;
+    const u16x2 size = pair_of(kTabSize);
     top = (u16x2){0, 0};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      top = __builtin_elementwise_max(top, tab_rare(t[k]));
-      t[k] = __builtin_elementwise_min(t[k], (u16x2)(uint16_t)kTabSize);
+      top = __builtin_elementwise_max(top, rare(t[k]));
+      t[k] = __builtin_elementwise_min(t[k], size);
     }
     if (__ballot(top[0] >= kTabSize || top[1] >= kTabSize) != 0) return false;
   }
@@ -1182,26 +1186,31 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
         }
         if (__ballot(top[0] >= kTabTinyAt || top[1] >= kTabTinyAt) != 0) {
           // zeros: counted (their terms are 1), then as good as -inf
+          const u16x2 tiny = pair_of(kTabTinyAt), none = pair_of(kTabZeroAt), one = pair_of(1);
           u16x2 n = {0, 0};
 #pragma unroll
           for (int i = 0; i < 2 * R; ++i) {
-            const u16x2 not0 = tab_not0(t[i]), keep = 0 - not0;
+            // (1, and then all bits, where an offset is not a zero's)
+            const u16x2 not0 = __builtin_elementwise_min((u16x2)((t[i] ^ tiny) >> 1), one);
+            const u16x2 keep = 0 - not0;
             n += not0;
-            t[i] = (t[i] & keep) | ((uint16_t)kTabZeroAt & ~keep);
+            t[i] = (t[i] & keep) | (none & ~keep);
           }
           n = (uint16_t)(2 * R) - n;
           s0 = (double)(uint16_t)(n[0] + n[1]);
         }
+        const TabRare rare;
+        const u16x2 size = pair_of(kTabSize);
 #pragma unroll
         for (int i = 0; i < 2 * R; ++i) {
-          const u16x2 r = tab_rare(t[i]);
+          const u16x2 r = rare(t[i]);
           if (__ballot(r[0] >= kTabNear || r[1] >= kTabNear) != 0) {
             uint32_t k2 = kTabUsual;
             s0 += tab_rare_term(r[0], k2);
             s1 += tab_rare_term(r[1], k2);
             if (__ballot(k2 != kTabUsual) != 0) kind = tab_raise(kind, k2);
           }
-          t[i] = __builtin_elementwise_min(t[i], (u16x2)(uint16_t)kTabSize);
+          t[i] = __builtin_elementwise_min(t[i], size);
         }
       }
       // (eight reads in flight: the scheduling barriers keep each batch whole)
@@ -1270,8 +1279,9 @@ __global__ void __launch_bounds__(kTabThreads) k_sample_tab(CacheArgs a) {
 __global__ void __launch_bounds__(kSmpThreads) k_sample_redo(CacheArgs a) {
   __shared__ SmpLds<kSmpThreads, kSmpMaxChunks> c;
   const int64_t row = xcd_remap(blockIdx.x, gridDim.x);
-  if ((a.mask && a.mask[row] == 0) || a.ids_out[row * a.K] != kSampleRedo) return;
-  // (every lane has read the mark before one overwrites it: sample_row has barriers)
+  // (a masked row's ids are 0; every lane has read the mark before one overwrites
+  // it: sample_row has barriers)
+  if (a.ids_out[row * a.K] != kSampleRedo) return;
   for (int j = threadIdx.x; j < kExpTab; j += kSmpThreads) c.tab[j] = exp2((double)j / kExpTab);
   __syncthreads();
   sample_row<InBf16, false>(a, row, (const char*)a.logits + row * a.ld * InBf16::BYTES, c);

@@ -223,8 +223,8 @@ def test_sample_stratified_uniforms_reproduce_the_distribution():
 def test_sample_table_rows(V, ld, N, M):
     """The table kernel's queue (several rows to a workgroup, masked ones among
     them) with rows of every kind: in the table's range, with magnitudes below
-    it (and zeros), with entries of no mass, and the kinds it leaves to the
-    general kernel (a logit of 64 or more, one in [-820, -64), undefined)."""
+    it (and zeros), with entries of no mass, undefined, and the kinds it leaves
+    to the general kernel (a magnitude of 640 or more, no mass to speak of)."""
     say("sample table V=%d N=%d M=%d" % (V, N, M))
     rng = np.random.default_rng(V + M)
     x = rng.normal(0.0, 3.0, (N, V)).astype(np.float32)
@@ -247,6 +247,8 @@ def test_sample_table_rows(V, ld, N, M):
         elif kind == 6:
             x[r, at[0]] = 63.5
             x[r, at[1]] = -63.5
+        elif kind == 7:
+            x[r, at[0]] = [700.0, -700.0][r // 16 % 2]
     stored = np.zeros((N, ld), np.uint16)
     stored[:, :V] = to_stored(x, synth.BF16)
     u = f32_uniforms(V + M, N, M)
@@ -286,11 +288,11 @@ def test_sample_both_sides_of_the_tables_rule(V, N, M):
 
 
 @pytest.mark.parametrize("edge", [-64.0, -63.75, -64.5])
-def test_sample_logits_at_the_tables_lower_edge(edge):
-    """Logits at and beside -64, the lower edge of the table kernel's values,
-    in rows where they matter: as nearly all of the row's mass below a maximum
-    of -59, as all of it, and as the first entry at a uniform of 0 (the first
-    entry of positive probability)."""
+def test_sample_rows_of_logits_near_minus_64(edge):
+    """Logits at and beside -64 in rows where they matter: as nearly all of the
+    row's mass below a maximum of -59 (its sum is just above the table kernel's
+    least), as all of it (below), and as the first entry at a uniform of 0 (the
+    first entry of positive probability)."""
     V, N, M = 16384, 4, 16
     x = np.full((N, V), edge, np.float32)
     x[0, 777] = -59.0
