@@ -17,9 +17,9 @@ using opd::Path;
 // rows over more workgroups outweighs the split path's second read of each
 // row.  Measured on MI355X (16-sample MC, V = 151,936 bf16, inputs rotated
 // so no step finds the last one's rows in the Infinity Cache), mean time per
-// call, split against row path: N = 8: 10.2 against 22.7 us; 24: 13.6 against
-// 23.3; 48: 17.9 against 23.6; 63: 19.6 against 23.9; more rows 128: 44.9
-// against 31.3.  Dense: N = 63: 25.2 against 30.5.
+// call, split against row path: N = 8: 9.8 against 22.7 us; 24: 13.9 against
+// 23.3; 48: 17.9 against 23.6; 63: 20.1 against 23.9; more rows 128: 44.9
+// against 31.3.  Dense: N = 63: 24.5 against 30.5.
 constexpr int64_t kSplitMaxRows = 64;
 // Workgroups the split path aims for below kSplitMaxRows: six to a CU, all of
 // them resident at once (two or three rounds of shorter ones repeat the rows'

@@ -774,10 +774,10 @@ __global__ void __launch_bounds__(kSmpThreads) k_sample(CacheArgs a) {
 // a uniform of 0 only (any other is at least 2^-149 of the sum), so a far row that
 // has one is marked too.
 // Measured at 4,096 rows of V = 151,936, 16 draws each, against k_sample for every
-// row: a tenth of the entries -inf 309 / 443 us, nine tenths 295 / 410, a tenth zeros
-// 394 / 430, one entry of 400 in every row 217 / 440, one of NaN 205 / 395; but one of 700
-// in every row (both kernels read it) 612 / 446, and every entry below 2^-17 and not 0
-// 654 / 405.
+// row: a tenth of the entries -inf 296 / 460 us, nine tenths 260 / 403, a tenth zeros
+// 354 / 414, one entry of 400 in every row 217 / 435, one of NaN 195 / 388; but one of
+// 700 in every row (both kernels read it) 600 / 430, and every entry below 2^-17
+// and not 0 597 / 401.
 //
 // One 1,024-lane workgroup per CU stays for all its rows, so the table is set
 // up once, and its 16 waves take work from one queue: for each row its tiles
@@ -787,10 +787,11 @@ __global__ void __launch_bounds__(kSmpThreads) k_sample(CacheArgs a) {
 // in a ring of slots.  A wave only ever waits for items before its own in the
 // queue (a draw for its row's tiles, a tile for the draws of the row that held
 // its slot), all of them held by running waves, so every wait ends.
-// Measured at 4,096 rows of V = 151,936, 16 draws each: 220 us (5.7 TB/s; a
-// plain read of the rows takes 183), against 430-450 us for k_sample, and 258
-// us with a workgroup, and a table, per row; 256 rows 29.4 / 53.5, 2,048 rows of V =
-// 20,000 43.2 / 65.  (The draws of chunks with unusual values are found one by one
+// Bound by HBM and LDS together: 220 us at 4,096 rows of V = 151,936, 16 draws each
+// (5.7 TB/s; a plain read of the rows takes 183), of which LDS bank
+// conflicts take about a third, against 430-450 us for k_sample, and 258 us with
+// a workgroup, and a table, per row; 256 rows 29.4 / 53.4, 2,048 rows of V = 20,000
+// 42.3 / 65.6.  (The draws of chunks with unusual values are found one by one
 // after the others, and the sums keep to the registers left: four copies of
 // the former, or an element's rare term beside each read, spill into the stream.)
 constexpr int kTabThreads = 1024;
@@ -798,7 +799,10 @@ constexpr int kTabRing = 2560;                  // records in the ring
 constexpr int kTabMaxSlots = 8;
 constexpr int kTabMaxChunks = kTabRing / 2;     // rows up to 655,360 entries
 constexpr int kTabCus = 256;
-constexpr int kTabDraws = 4;                    // draws per item
+// Draws per item.  Two cost 16 draws of 4,096 rows 229 against 219 us, 64 draws of
+// 2,048 rows of V = 20,000 99 / 85 (256 rows 26.9 / 28.7); eight spill, 228 / 214 and
+// 256 rows 36.0 / 28.7 (64 draws 300 / 318).
+constexpr int kTabDraws = 4;
 constexpr uint32_t kTabLoExp = 110;             // biased exponent of 2^-17
 constexpr uint32_t kTabBase = kTabLoExp << 7;   // bf16 magnitude bits of 2^-17
 constexpr uint32_t kTabEnd = 0x4420;            // of 640

@@ -26,9 +26,11 @@
 // rho >= 0, so its bits order like values.  Integer histograms make the
 // selection exact and order-independent; every floating-point sum has a fixed
 // order.  Measured (32,768 tokens, M = 16, three group sizes, 2,048-token
-// sequences): 38 us a call (rows 16, mid 5.5, low 5, final 10), against 116 in
-// thirteen launches with a launch each for the parts and each bucket's choice
-// and four passes of 8 bits.
+// sequences): 36 us a call (rows 18.9, mid 4.8, low 9.5, final 5.5 in a trace),
+// against 116 in thirteen launches with a launch each for the parts and each
+// bucket's choice and four passes of 8 bits, and 38 with the set variances in the
+// final launch, where 2,048 sequences of one token and 256 draws took 13.6 ms (36
+// us so).
 #include <math.h>
 
 #include "opd_device.h"
